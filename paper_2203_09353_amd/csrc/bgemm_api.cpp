@@ -273,12 +273,15 @@ bg_status_t bg_gemm_batched_mode(bg_handle_t h, int mode, int slices, char trans
     a.alpha = alpha; a.beta = beta;
     a.A = dA; a.lda = lda; a.B = dB; a.ldb = ldb; a.C = dC; a.ldc = ldc;
     a.batch = batch;
+    a.num_cus = h->num_cus;
     if (mode == BG_MODE_EMU_I8) {
       // exact int32 diagonal sums need k <= 8192; the exponents of at least
       // one instance must fit the workspace
       if (k > 8192) return BG_STATUS_NOT_SUPPORTED;
       if (h->ws_bytes < (size_t)(m + n) * sizeof(int)) return BG_STATUS_ALLOC_FAILED;
       e = bg::launch_emu8(a, slices, h->ws, h->ws_bytes, h->stream);
+    } else if (mode == BG_MODE_FP32 || mode == BG_MODE_BF16) {
+      e = bg::launch_rounded(a, mode, h->stream);
     } else {
       e = bg::launch_uniform_lowp(a, mode, slices, h->stream);
     }

@@ -41,9 +41,12 @@ struct UniformArgs {
 // Launches the uniform batched GEMM (product path; alpha != 0, k > 0).
 hipError_t launch_uniform(const UniformArgs& a, TileClass cls, hipStream_t s);
 
-// Reduced / emulated precision modes of the uniform batch (NN operands only):
-// mode 1 binary32, 2 bfloat16, 3 emulated binary64 with `slices` (1..8)
-// bfloat16 digit slices.  hipErrorInvalidValue for grids beyond int32.
+// Reduced precision modes of the uniform batch (NN operands only): mode 1
+// binary32, 2 bfloat16.  hipErrorInvalidValue for grids beyond int32.
+hipError_t launch_rounded(const UniformArgs& a, int mode, hipStream_t s);
+// Emulated precision modes (NN operands only): mode 3 emulated binary64 with
+// `slices` (1..8) bfloat16 digit slices, 5 the same digits summed in binary32.
+// hipErrorInvalidValue for grids beyond int32.
 hipError_t launch_uniform_lowp(const UniformArgs& a, int mode, int slices, hipStream_t s);
 // Emulated binary64 on int8 digit slices (NN, k <= 8192): per group of
 // instances, row / column exponents into the workspace (m + n ints per

@@ -1,11 +1,7 @@
-// Reduced- and emulated-precision batched GEMM modes for gfx950.
+// Emulated-precision batched GEMM modes for gfx950 on bfloat16-sized digits.
 //
 // Same operation as the FP64 path (the paper, Section II, Eq. 1), on binary64
 // inputs and outputs, with cheaper inner arithmetic:
-//   fp32 : inputs rounded to binary32, products and sums on the binary32
-//          matrix cores (v_mfma_f32_16x16x4_f32);
-//   bf16 : inputs rounded to binary32 then bfloat16 (nearest even), binary32
-//          accumulation (v_mfma_f32_16x16x32_bf16);
 //   emu  : emulated binary64 from S bfloat16 digit slices.  Per 32-wide chunk
 //          of k, row i of A and column j of B are scaled by powers of two
 //          2^-e_i, 2^-f_j (frexp exponent of the chunk's largest magnitude)
@@ -25,8 +21,8 @@
 //
 // Tile: 64 x 64 of C per workgroup (four waves of 32 x 32, i.e. 2 x 2 blocks
 // of 16 x 16), one 32-wide chunk of k per step.  Each step stages the binary64
-// tiles in LDS, converts them to the mode's operand tiles in LDS (k
-// contiguous per row of A / column of B), then runs the matrix-core
+// tiles in LDS, converts them to digit tiles in LDS (k contiguous per row of
+// A / column of B), then runs the matrix-core
 // instructions.  The instruction's first operand is B's tile and its second
 // A's, so a result block is the transpose of a C block and its 16 lanes cover
 // 16 consecutive rows of a C column (coalesced epilogue).  Operands must be
@@ -49,20 +45,13 @@ typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 constexpr int BM = 64, BN = 64, BKC = 32, NT = 256;
 constexpr int S64A = BM + 2;    // staging A: [k][m], doubles
 constexpr int S64B = BKC + 1;   // staging B: [n][k], doubles
-constexpr int SF = BKC + 4;     // fp32 operand rows (floats): bank-distinct 4-byte reads
 constexpr int SH = BKC + 8;     // bf16 operand rows (halves): 80-byte stride, distinct 16-byte reads
 
-enum Mode { FP32 = 1, BF16 = 2, EMU = 3, EMU32 = 5 };
+enum Mode { EMU = 3, EMU32 = 5 };
 
 // a digit held as bfloat16 bits, as the binary32 value it represents (exact)
 __device__ __forceinline__ float bf16_to_f32(unsigned short h) {
   return __uint_as_float((unsigned int)h << 16);
-}
-
-__device__ __forceinline__ unsigned short bf16_rne(float f) {
-  unsigned int u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
 }
 
 // a value that bfloat16 holds exactly (a digit): its top 16 bits
@@ -70,19 +59,13 @@ __device__ __forceinline__ unsigned short bf16_exact(float f) {
   return (unsigned short)(__float_as_uint(f) >> 16);
 }
 
-// the digit-slice modes
-constexpr bool is_emu(int mode) { return mode == EMU || mode == EMU32; }
-
-template <int MODE, int S>
+template <int S>
 struct __align__(16) Smem {
-  static constexpr int NSL = is_emu(MODE) ? S : 1;
   double a64[BKC * S64A];
   double b64[BN * S64B];
   int ea[BM], fb[BN];
-  union {
-    struct { float a[BM * SF]; float b[BN * SF]; } f32;
-    struct { unsigned short a[NSL][BM * SH]; unsigned short b[NSL][BN * SH]; } h16;
-  } op;
+  unsigned short da[S][BM * SH];
+  unsigned short db[S][BN * SH];
 };
 
 template <int MODE, int S>
@@ -95,8 +78,8 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
   // every binary64 rounding below is the one written (no fused multiply-add),
   // which is what makes the emulated mode reproducible bit for bit
 #pragma clang fp contract(off)
-  __shared__ Smem<MODE, S> sm;
-  constexpr int NG = is_emu(MODE) ? S : 1;   // accumulator sets (diagonals g = 2..S+1)
+  __shared__ Smem<S> sm;
+  constexpr int NG = S;   // accumulator sets (diagonals g = 2..S+1)
   const int64_t bid = blockIdx.x;
   const int64_t id = (bid % 8) * per_xcd + bid / 8;   // contiguous tiles per XCD
   if (id >= total_tiles) return;
@@ -144,24 +127,22 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
       sm.b64[c * S64B + kk] = (gc < N && gk < K) ? B[gk + (int64_t)gc * ldb] : 0.0;
     }
     __syncthreads();
-    // 2. (emu) chunk exponents of the 64 rows of A and 64 columns of B
-    if constexpr (is_emu(MODE)) {
-      if (tid < BM) {
-        double mx = 0.0;
-        for (int kk = 0; kk < BKC; ++kk) mx = fmax(mx, fabs(sm.a64[kk * S64A + tid]));
-        int e = 0;
-        if (mx > 0.0) frexp(mx, &e);
-        sm.ea[tid] = e;
-      } else if (tid < BM + BN) {
-        const int c = tid - BM;
-        double mx = 0.0;
-        for (int kk = 0; kk < BKC; ++kk) mx = fmax(mx, fabs(sm.b64[c * S64B + kk]));
-        int e = 0;
-        if (mx > 0.0) frexp(mx, &e);
-        sm.fb[c] = e;
-      }
-      __syncthreads();
+    // 2. chunk exponents of the 64 rows of A and 64 columns of B
+    if (tid < BM) {
+      double mx = 0.0;
+      for (int kk = 0; kk < BKC; ++kk) mx = fmax(mx, fabs(sm.a64[kk * S64A + tid]));
+      int e = 0;
+      if (mx > 0.0) frexp(mx, &e);
+      sm.ea[tid] = e;
+    } else if (tid < BM + BN) {
+      const int c = tid - BM;
+      double mx = 0.0;
+      for (int kk = 0; kk < BKC; ++kk) mx = fmax(mx, fabs(sm.b64[c * S64B + kk]));
+      int e = 0;
+      if (mx > 0.0) frexp(mx, &e);
+      sm.fb[c] = e;
     }
+    __syncthreads();
     // 3. operand tiles: thread handles 8 consecutive k of one row of A and of
     //    one column of B (row / column = tid % 64, k block = tid / 64)
     {
@@ -172,63 +153,31 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
         xa[e] = sm.a64[(kb + e) * S64A + r];
         xb[e] = sm.b64[r * S64B + kb + e];
       }
-      if constexpr (MODE == FP32) {
+      const int ea = sm.ea[r], fb = sm.fb[r];
+      double ra[8], rb[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          sm.op.f32.a[r * SF + kb + e] = (float)xa[e];
-          sm.op.f32.b[r * SF + kb + e] = (float)xb[e];
-        }
-      } else if constexpr (MODE == BF16) {
+      for (int e = 0; e < 8; ++e) {
+        ra[e] = ldexp(xa[e], -ea) * 128.0;
+        rb[e] = ldexp(xb[e], -fb) * 128.0;
+      }
+#pragma unroll
+      for (int t = 0; t < S; ++t) {
         u16x8 ha, hb;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          ha[e] = bf16_rne((float)xa[e]);
-          hb[e] = bf16_rne((float)xb[e]);
+          const double da = rint(ra[e]), db = rint(rb[e]);
+          ha[e] = bf16_exact((float)da);
+          hb[e] = bf16_exact((float)db);
+          ra[e] = (ra[e] - da) * 256.0;
+          rb[e] = (rb[e] - db) * 256.0;
         }
-        *(u16x8*)&sm.op.h16.a[0][r * SH + kb] = ha;
-        *(u16x8*)&sm.op.h16.b[0][r * SH + kb] = hb;
-      } else {
-        const int ea = sm.ea[r], fb = sm.fb[r];
-        double ra[8], rb[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          ra[e] = ldexp(xa[e], -ea) * 128.0;
-          rb[e] = ldexp(xb[e], -fb) * 128.0;
-        }
-#pragma unroll
-        for (int t = 0; t < S; ++t) {
-          u16x8 ha, hb;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const double da = rint(ra[e]), db = rint(rb[e]);
-            ha[e] = bf16_exact((float)da);
-            hb[e] = bf16_exact((float)db);
-            ra[e] = (ra[e] - da) * 256.0;
-            rb[e] = (rb[e] - db) * 256.0;
-          }
-          *(u16x8*)&sm.op.h16.a[t][r * SH + kb] = ha;
-          *(u16x8*)&sm.op.h16.b[t][r * SH + kb] = hb;
-        }
+        *(u16x8*)&sm.da[t][r * SH + kb] = ha;
+        *(u16x8*)&sm.db[t][r * SH + kb] = hb;
       }
     }
     __syncthreads();
     // 4. matrix-core products
-    if constexpr (MODE == FP32) {
-#pragma unroll
-      for (int ks = 0; ks < BKC; ks += 4) {
-        float fa[2], fbv[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          fa[b] = sm.op.f32.a[(wm0 + 16 * b + li) * SF + ks + lg];
-          fbv[b] = sm.op.f32.b[(wn0 + 16 * b + li) * SF + ks + lg];
-        }
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-          for (int bj = 0; bj < 2; ++bj)
-            acc32[0][bi][bj] = __builtin_amdgcn_mfma_f32_16x16x4f32(fbv[bj], fa[bi], acc32[0][bi][bj], 0, 0, 0);
-      }
-    } else if constexpr (MODE == EMU32) {
+    if constexpr (MODE == EMU32) {
       // per diagonal pair (t, u): eight 4-wide steps of k on the binary32
       // matrix cores; lane (li, lg) takes digit k = ks + lg of row / column li
 #pragma unroll
@@ -242,8 +191,8 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
             float fa[2], fbv[2];
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-              fa[b] = bf16_to_f32(sm.op.h16.a[t - 1][(wm0 + 16 * b + li) * SH + ks + lg]);
-              fbv[b] = bf16_to_f32(sm.op.h16.b[u - 1][(wn0 + 16 * b + li) * SH + ks + lg]);
+              fa[b] = bf16_to_f32(sm.da[t - 1][(wm0 + 16 * b + li) * SH + ks + lg]);
+              fbv[b] = bf16_to_f32(sm.db[u - 1][(wn0 + 16 * b + li) * SH + ks + lg]);
             }
 #pragma unroll
             for (int bi = 0; bi < 2; ++bi)
@@ -256,19 +205,19 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
       }
     } else {
 #pragma unroll
-      for (int t = 1; t <= (MODE == EMU ? S : 1); ++t) {
+      for (int t = 1; t <= S; ++t) {
         bf8 va[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-          va[b] = __builtin_bit_cast(bf8, *(const u16x8*)&sm.op.h16.a[t - 1][(wm0 + 16 * b + li) * SH + 8 * lg]);
+          va[b] = __builtin_bit_cast(bf8, *(const u16x8*)&sm.da[t - 1][(wm0 + 16 * b + li) * SH + 8 * lg]);
 #pragma unroll
-        for (int u = 1; u <= (MODE == EMU ? S : 1); ++u) {
-          if (t + u > S + 1 && MODE == EMU) continue;
+        for (int u = 1; u <= S; ++u) {
+          if (t + u > S + 1) continue;
           bf8 vb[2];
 #pragma unroll
           for (int b = 0; b < 2; ++b)
-            vb[b] = __builtin_bit_cast(bf8, *(const u16x8*)&sm.op.h16.b[u - 1][(wn0 + 16 * b + li) * SH + 8 * lg]);
-          const int g = MODE == EMU ? t + u - 2 : 0;
+            vb[b] = __builtin_bit_cast(bf8, *(const u16x8*)&sm.db[u - 1][(wn0 + 16 * b + li) * SH + 8 * lg]);
+          const int g = t + u - 2;
 #pragma unroll
           for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
@@ -277,31 +226,27 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
         }
       }
     }
-    if constexpr (MODE != FP32) {
-      // 5. (emu) fold this chunk into binary64 in the fixed order
-      if constexpr (is_emu(MODE)) {
+    // 5. fold this chunk into binary64 in the fixed order
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-          for (int bj = 0; bj < 2; ++bj)
+      for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              // lane holds C(row = wm0 + 16 bi + li, col = wn0 + 16 bj + 4 lg + v)
-              double T = 0.0;
+        for (int v = 0; v < 4; ++v) {
+          // lane holds C(row = wm0 + 16 bi + li, col = wn0 + 16 bj + 4 lg + v)
+          double T = 0.0;
 #pragma unroll
-              for (int g = S - 1; g >= 0; --g)   // diagonal t + u = g + 2, largest first
-                T = T + (double)acc32[g][bi][bj][v] * ldexp(1.0, -14 - 8 * g);
-              const int er = sm.ea[wm0 + 16 * bi + li], fc = sm.fb[wn0 + 16 * bj + 4 * lg + v];
-              acc64[bi][bj][v] = acc64[bi][bj][v] + ldexp(T, er + fc);
-            }
+          for (int g = S - 1; g >= 0; --g)   // diagonal t + u = g + 2, largest first
+            T = T + (double)acc32[g][bi][bj][v] * ldexp(1.0, -14 - 8 * g);
+          const int er = sm.ea[wm0 + 16 * bi + li], fc = sm.fb[wn0 + 16 * bj + 4 * lg + v];
+          acc64[bi][bj][v] = acc64[bi][bj][v] + ldexp(T, er + fc);
+        }
 #pragma unroll
-        for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-          for (int bi = 0; bi < 2; ++bi)
+      for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj) acc32[g][bi][bj] = f4{0.f, 0.f, 0.f, 0.f};
-      }
-    }
+        for (int bj = 0; bj < 2; ++bj) acc32[g][bi][bj] = f4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();   // before the next chunk overwrites the LDS tiles
   }
 
@@ -331,8 +276,7 @@ __global__ __launch_bounds__(NT) void k_lowp(int M, int N, int K, double alpha,
           if (beta == 1.0) continue;
           x = beta == 0.0 ? 0.0 : beta * cv[bi][bj][v];
         } else {
-          const double p = is_emu(MODE) ? acc64[bi][bj][v] : (double)acc32[0][bi][bj][v];
-          x = alpha * p;
+          x = alpha * acc64[bi][bj][v];
           if (beta != 0.0) x = x + beta * cv[bi][bj][v];
         }
         C[row + (int64_t)col * ldc] = x;
@@ -356,8 +300,6 @@ static hipError_t launch(const UniformArgs& a, hipStream_t s) {
 
 hipError_t launch_uniform_lowp(const UniformArgs& a, int mode, int slices, hipStream_t s) {
   using namespace lowp;
-  if (mode == FP32) return launch<FP32, 1>(a, s);
-  if (mode == BF16) return launch<BF16, 1>(a, s);
   if (mode == EMU32) {
     switch (slices) {
       case 1: return launch<EMU32, 1>(a, s);

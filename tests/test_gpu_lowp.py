@@ -150,6 +150,28 @@ def test_reduced_modes_within_binary32_accumulation(h, mode, m, n, k):
             assert np.all(np.abs(G - exp) <= bound), (mode, m, n, k)
 
 
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+@pytest.mark.parametrize("m,n,k,batch", [(128, 128, 32, 520), (127, 121, 33, 520),
+                                         (65, 66, 1, 520), (256, 254, 95, 130),
+                                         (129, 128, 64, 270), (64, 64, 31, 3)])
+def test_reduced_modes_tile_edges(h, mode, m, n, k, batch):
+    """Both tile shapes at their edges (the larger one serves batches of at
+    least two tiles per CU): each instance within the binary32 bound, and the
+    same bits as when it runs alone, through the smaller tile."""
+    A, B, C = _operands(91, m, n, k, batch, (1, 0, 3), 0)
+    Ad, Bd, Cd = A.cuda(), B.cuda(), C.cuda()
+    h.batched_mode(mode, Ad, Bd, Cd, m, n, k, -0.75, 1.5)
+    for i in (0, batch // 2, batch - 1):
+        C1 = C[i:i + 1].cuda()
+        h.batched_mode(mode, Ad[i:i + 1], Bd[i:i + 1], C1, m, n, k, -0.75, 1.5)
+        got = Cd[i].cpu().numpy()
+        assert np.array_equal(got.view(np.int64), C1[0].cpu().numpy().view(np.int64)), i
+        Am, Bm, C0 = _mat(A[i].numpy(), m), _mat(B[i].numpy(), k), _mat(C[i].numpy(), m)
+        exp = -0.75 * P.reference_product(Am, Bm, mode) + 1.5 * C0
+        bound = _reduced_bound(mode, Am, Bm, 0.75) + 1e-15 * (np.abs(exp) + 1.5 * np.abs(C0))
+        assert np.all(np.abs(_mat(got, m) - exp) <= bound), (mode, m, n, k, i)
+
+
 @pytest.mark.parametrize("mode,lo", [("fp32", 1e-9), ("bf16", 1e-4)])
 def test_reduced_modes_really_reduce(h, mode, lo):
     G, Am, Bm, _ = run_mode(h, mode, 0, 64, 64, 64, seed=51, batch=1)[0]
