@@ -107,7 +107,7 @@ bg_status_t bs_fill_factor(unsigned long long seed, int c, long long j, int n, d
 /* Annealing sweeps in lock step: every client receives `chain` products
  * per sweep (same factors and states as requests of that length would
  * give), `sweeps` times.  With use_graph != 0 one sweep (a factor launch and
- * one batched launch per size per product, then an update of the product
+ * the products' batches per product, then an update of the product
  * counters on the device) is captured once as a HIP graph -- two when chain
  * is odd, one per ping-pong parity -- and replayed on the handle's stream
  * (the capture itself runs on a private stream, since the null stream cannot
@@ -134,7 +134,8 @@ bg_status_t bs_memory_stats(bs_server_t s, unsigned long long* pool_bytes,
 #define BS_TICK_PER_SIZE 0
 #define BS_TICK_VBATCHED 1
 /* How a tick's products are launched: BS_TICK_PER_SIZE (default), one
- * bg_dgemm_batched per distinct client size; BS_TICK_VBATCHED, one
+ * uniform batch per distinct client size (batches too short to fill the chip
+ * share a launch); BS_TICK_VBATCHED, one
  * bg_dgemm_vbatched over every product of the tick (sizes uploaded with the
  * pointers, planned on the device; it uses the handle's workspace).  Results
  * are bit-identical either way. */

@@ -84,6 +84,25 @@ VbatchedArgs vbatched_args(char transa, char transb, const int* d_m, const int* 
   return a;
 }
 
+bg_status_t dgemm_square_groups(bg_handle_t h, const SquareGroup* groups, int count) {
+  if (!valid(h)) return BG_STATUS_INVALID_HANDLE;
+  h->last_invalid_arg = 0;
+  if (h->force_class >= 0) {
+    for (int i = 0; i < count; ++i) {
+      const SquareGroup& q = groups[i];
+      const bg_status_t st = bg_dgemm_batched(h, 'N', 'N', q.n, q.n, q.n, 1.0, q.A, q.n, q.B, q.n,
+                                              0.0, q.C, q.n, q.batch);
+      if (st != BG_STATUS_SUCCESS) return st;
+    }
+    return BG_STATUS_SUCCESS;
+  }
+  DeviceGuard guard(h->device);
+  if (!guard.ok) return BG_STATUS_DEVICE_ERROR;
+  return launch_square_groups(groups, count, h->num_cus, h->stream) == hipSuccess
+             ? BG_STATUS_SUCCESS
+             : BG_STATUS_DEVICE_ERROR;
+}
+
 }  // namespace bg
 
 extern "C" {

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "../../include/bgemm.h"
+
 namespace bg {
 
 // Tile shapes.  A "size class" is one tile configuration of the MFMA tile
@@ -15,11 +17,10 @@ enum TileClass : int {
   TC_32 = 0,     // 32 x 32 tile         (tiny matrices)
   TC_64 = 1,     // 64 x 64 tile         (small matrices, short batches)
   TC_128 = 2,    // 128 x 64 tile        (large matrices)
-  TC_COUNT = 3
+  TC_COUNT = 3,  // classes a caller can force
+  TC_64S = 3,    // 64 x 64 tile, eight waves, direct-load pipeline (short batches)
+  TC_64x32 = 4   // 64 x 32 tile, four waves, 32 of k per step (the shortest batches)
 };
-
-struct TileShape { int bm, bn, bk, threads; };
-TileShape tile_shape(TileClass c);
 
 // Picks the tile class for a uniform batch of `batch` instances on a device
 // of `num_cus` compute units; `force` >= 0 overrides.
@@ -40,6 +41,19 @@ struct UniformArgs {
 
 // Launches the uniform batched GEMM (product path; alpha != 0, k > 0).
 hipError_t launch_uniform(const UniformArgs& a, TileClass cls, hipStream_t s);
+
+// Batches of n x n products C_i <- A_i B_i (ld = n), one per size: short batches
+// share launches, in the given order; a batch that fills the chip runs alone.
+struct SquareGroup {
+  int n, batch;
+  const double* const* A;
+  const double* const* B;
+  double* const* C;
+};
+hipError_t launch_square_groups(const SquareGroup* groups, int count, int num_cus, hipStream_t s);
+// The same on a handle's device and stream (one call per size when the caller
+// has forced a tile class on the handle).
+bg_status_t dgemm_square_groups(bg_handle_t h, const SquareGroup* groups, int count);
 
 // Reduced precision modes of the uniform batch (NN operands only): mode 1
 // binary32, 2 bfloat16.  hipErrorInvalidValue for grids beyond int32.
@@ -119,7 +133,7 @@ hipError_t launch_gate2(int S, const int* sites, const double* const* U, double*
 
 // Request loop: one generated factor (column-major n x n at `out`; factor j of
 // `client`, values scaled by `scale`).
-struct FillJob {
+struct FillJob {   // 8-byte aligned, a multiple of 8 bytes: pointers may follow an array of them
   double* out;
   long long j;
   int n;

@@ -148,6 +148,14 @@ struct Cfg {
 #endif
 using Cfg32 = Cfg<BG_CFG32>;
 using Cfg64 = Cfg<BG_CFG64>;
+// Short batches (latency-bound: a CU holds one or two tiles, so a tile's own
+// k loop is the critical path).  Eight waves of 16 x 32 on the three-stage
+// pipeline: 7 x 512^3 took 48.7 us on the four-wave register path, 44.9 on
+// four pipelined waves and 40.8 on eight; 20 x 256^3 26.2 / 25.2 / 22.8.  Four
+// stages, or 32 of k per step, were no faster (41.5, 48.6 us).
+using Cfg64S = Cfg<64, 64, 16, 16, 32, true, 2, false, 1, 3>;
+// The shortest batches: half the tile, so twice the CUs, 32 of k per step
+using Cfg64x32 = Cfg<64, 32, 32, 16, 32, true, 2, false, 1, 3>;
 using Cfg128 = Cfg<BG_CFG128>;
 
 // ---------------------------------------------------------------------------
@@ -1083,14 +1091,6 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
   return launch_uniform_t<CF, true, true>(a, s);
 }
 
-TileShape tile_shape(TileClass c) {
-  switch (c) {
-    case TC_32: return {Cfg32::BM, Cfg32::BN, Cfg32::BK, Cfg32::NT};
-    case TC_64: return {Cfg64::BM, Cfg64::BN, Cfg64::BK, Cfg64::NT};
-    default: return {Cfg128::BM, Cfg128::BN, Cfg128::BK, Cfg128::NT};
-  }
-}
-
 TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int force) {
   (void)k;
   if (force >= 0 && force < TC_COUNT) return (TileClass)force;
@@ -1099,19 +1099,115 @@ TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int fo
   if (mx <= 64) return TC_64;
   // A batch too small to give every CU two 128 x 64 tiles is spread over
   // twice as many 64 x 64 tiles instead (a short batch is latency-bound:
-  // more, shorter tiles finish sooner).
+  // more, shorter tiles finish sooner), and one whose 64 x 64 tiles do not
+  // reach every CU over 64 x 32 tiles: 1 x 512^3 25.5 us on 64 x 64 and 18.6 on
+  // 64 x 32 tiles, 8 x 256^3 14.9 / 11.2, but 20 x 256^3 22.8 / 23.6 and 7 x
+  // 512^3 40.8 / 49.5.
   const int64_t tiles128 = (int64_t)((m + Cfg128::BM - 1) / Cfg128::BM) *
                            ((n + Cfg128::BN - 1) / Cfg128::BN) * batch;
-  if (tiles128 < 2 * (int64_t)num_cus) return TC_64;
-  return TC_128;
+  if (tiles128 >= 2 * (int64_t)num_cus) return TC_128;
+  const int64_t tiles64 = (int64_t)((m + 63) / 64) * ((n + 63) / 64) * batch;
+  return tiles64 <= num_cus ? TC_64x32 : TC_64S;
 }
 
 hipError_t launch_uniform(const UniformArgs& a, TileClass cls, hipStream_t s) {
   switch (cls) {
     case TC_32: return launch_uniform_c<Cfg32>(a, s);
     case TC_64: return launch_uniform_c<Cfg64>(a, s);
+    case TC_64S: return launch_uniform_c<Cfg64S>(a, s);
+    case TC_64x32: return launch_uniform_c<Cfg64x32>(a, s);
     default: return launch_uniform_c<Cfg128>(a, s);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Several short batches of square products in one launch (the request loop's
+// tick: one batch per client size).  Launched one after another each of them
+// leaves most of the chip idle and waits for its own slowest tile; here the
+// tiles of all of them are in flight together, largest matrices first.  Each
+// batch's tiles are dealt to the XCDs in contiguous ranges, as in k_uniform.
+// What bounds it is the largest matrices' k loop on the CUs that hold two of
+// their tiles.  Measured on a tick of 32 clients (sizes 32..512, seven of
+// 512): five launches 92 us, one 47; draining 2,000 requests of 1..16 products
+// 86 -> 52 ms.
+// ---------------------------------------------------------------------------
+constexpr int MAX_GROUPS = 16;
+
+struct GroupTable {
+  int count;
+  int n[MAX_GROUPS];
+  int tiles[MAX_GROUPS];          // C tiles of the batch
+  int slot[MAX_GROUPS + 1];       // first workgroup of the batch on each XCD
+  const double* const* A[MAX_GROUPS];
+  const double* const* B[MAX_GROUPS];
+  double* const* C[MAX_GROUPS];
+};
+
+template <class CF>
+__global__ __launch_bounds__(CF::NT) void k_uniform_groups(GroupTable gt) {
+  __shared__ double lds[TileSmem<CF, false, false>::TOTAL];
+  const int x = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD;
+  int g = 0;
+  while (g + 1 < gt.count && slot >= gt.slot[g + 1]) ++g;
+  const int id = x * (gt.slot[g + 1] - gt.slot[g]) + slot - gt.slot[g];
+  if (id >= gt.tiles[g]) return;
+  const int n = gt.n[g];
+  const int tiles_m = (n + CF::BM - 1) / CF::BM, tpi = tiles_m * ((n + CF::BN - 1) / CF::BN);
+  const int inst = id / tpi, t = id - inst * tpi;
+  gemm_tile<CF, false, false>(gt.A[g][inst], n, gt.B[g][inst], n, gt.C[g][inst], n, n, n, n, 1.0,
+                              0.0, t % tiles_m, t / tiles_m, (lptr)lds);
+}
+
+template <class CF>
+static hipError_t launch_groups(const GroupTable& gt, hipStream_t s) {
+  hipLaunchKernelGGL((k_uniform_groups<CF>), dim3((unsigned)(gt.slot[gt.count] * NUM_XCD)),
+                     dim3(CF::NT), 0, s, gt);
+  return hipGetLastError();
+}
+
+hipError_t launch_square_groups(const SquareGroup* groups, int count, int num_cus, hipStream_t s) {
+  auto fills_chip = [&](const SquareGroup& q) {
+    return (int64_t)((q.n + Cfg128::BM - 1) / Cfg128::BM) *
+               ((q.n + Cfg128::BN - 1) / Cfg128::BN) * q.batch >= 2 * (int64_t)num_cus;
+  };
+  int64_t tiles64 = 0;
+  for (int i = 0; i < count; ++i) {
+    const SquareGroup& q = groups[i];
+    if (!fills_chip(q)) {
+      tiles64 += (int64_t)((q.n + 63) / 64) * ((q.n + 63) / 64) * q.batch;
+      continue;
+    }
+    UniformArgs a;
+    a.ta = a.tb = false;
+    a.m = a.n = a.k = q.n;
+    a.alpha = 1.0; a.beta = 0.0;
+    a.A = q.A; a.lda = q.n; a.B = q.B; a.ldb = q.n; a.C = q.C; a.ldc = q.n;
+    a.batch = q.batch;
+    const hipError_t e =
+        launch_uniform(a, pick_uniform_class(q.n, q.n, q.n, q.batch, num_cus, -1), s);
+    if (e != hipSuccess) return e;
+  }
+  // the short ones, MAX_GROUPS to a launch; tile shapes as for one short batch
+  const bool narrow = tiles64 <= num_cus;
+  GroupTable gt;
+  gt.count = 0;
+  gt.slot[0] = 0;
+  for (int i = 0; i < count; ++i) {
+    const SquareGroup& q = groups[i];
+    if (fills_chip(q)) continue;
+    const int g = gt.count++;
+    gt.n[g] = q.n;
+    gt.tiles[g] = ((q.n + 63) / 64) * ((q.n + (narrow ? 31 : 63)) / (narrow ? 32 : 64)) * q.batch;
+    gt.slot[g + 1] = gt.slot[g] + (gt.tiles[g] + NUM_XCD - 1) / NUM_XCD;
+    gt.A[g] = q.A; gt.B[g] = q.B; gt.C[g] = q.C;
+    if (gt.count == MAX_GROUPS) {
+      const hipError_t e = narrow ? launch_groups<Cfg64x32>(gt, s) : launch_groups<Cfg64S>(gt, s);
+      if (e != hipSuccess) return e;
+      gt.count = 0;
+    }
+  }
+  if (gt.count == 0) return hipSuccess;
+  return narrow ? launch_groups<Cfg64x32>(gt, s) : launch_groups<Cfg64S>(gt, s);
 }
 
 // C_i <- beta * C_i, or exactly 0 when beta == 0 (C not read).

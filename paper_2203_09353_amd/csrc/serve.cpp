@@ -227,10 +227,9 @@ struct bs_server {
   std::vector<long long> products;
   // two sets of job / pointer arrays, so one tick can be prepared while the
   // previous one runs
-  bg::FillJob* d_jobs[2];
-  bg::FillJob* h_jobs[2];         // pinned
-  const double** d_ptrs[2];
-  const double** h_ptrs[2];       // pinned
+  // a tick's arrays, one upload: the factor jobs, then three pointers per job
+  char* d_tick[2];
+  char* h_tick[2];                 // pinned
   // per-instance sizes and leading dimensions of a tick's variable-size
   // launch: m, n, k, lda, ldb, ldc, each num_clients ints
   int* d_dims[2];
@@ -248,19 +247,16 @@ static bool valid(bs_server_t s) { return s && s->magic == kServerMagic; }
 
 static size_t state_bytes(int n) { return 2 * (size_t)n * (size_t)n * sizeof(double); }
 static size_t factor_bytes(int n) { return bs::Pool::round((size_t)n * (size_t)n * sizeof(double)); }
-static size_t array_bytes(int nc) {
-  return 2ull * nc * (sizeof(bg::FillJob) + 3 * sizeof(double*) + 6 * sizeof(int));
-}
+static size_t tick_bytes(int nc) { return (size_t)nc * (sizeof(bg::FillJob) + 3 * sizeof(double*)); }
+static size_t array_bytes(int nc) { return 2 * (tick_bytes(nc) + 6ull * nc * sizeof(int)); }
 
 static void free_all(bs_server* s) {
   for (int b = 0; b < 2; ++b)
     for (double* p : s->st[b]) if (p) (void)hipFree(p);
   if (s->pool_base) (void)hipFree(s->pool_base);
   for (int b = 0; b < 2; ++b) {
-    if (s->d_jobs[b]) (void)hipFree(s->d_jobs[b]);
-    if (s->d_ptrs[b]) (void)hipFree((void*)s->d_ptrs[b]);
-    if (s->h_jobs[b]) (void)hipHostFree(s->h_jobs[b]);
-    if (s->h_ptrs[b]) (void)hipHostFree((void*)s->h_ptrs[b]);
+    if (s->d_tick[b]) (void)hipFree(s->d_tick[b]);
+    if (s->h_tick[b]) (void)hipHostFree(s->h_tick[b]);
     if (s->d_dims[b]) (void)hipFree(s->d_dims[b]);
     if (s->h_dims[b]) (void)hipHostFree(s->h_dims[b]);
     if (s->ev[b]) (void)hipEventDestroy(s->ev[b]);
@@ -274,6 +270,23 @@ static hipError_t set_identity(bs_server* s, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   return hipStreamSynchronize(stream);
+}
+
+// The products of `count` clients in `order` (equal sizes adjacent, largest
+// first): ptrs holds `count` factor pointers, then as many states in and out
+// (device array).  One batch per size, the short ones in one launch.
+static bg_status_t multiply(bs_server* s, const std::vector<int>& order, const double* const* ptrs,
+                            int count) {
+  std::vector<bg::SquareGroup> groups;
+  for (int g0 = 0; g0 < count;) {
+    int g1 = g0;
+    const int n = s->sizes[order[g0]];
+    while (g1 < count && s->sizes[order[g1]] == n) ++g1;
+    groups.push_back(bg::SquareGroup{n, g1 - g0, ptrs + g0, ptrs + count + g0,
+                                     (double* const*)(ptrs + 2 * count + g0)});
+    g0 = g1;
+  }
+  return bg::dgemm_square_groups(s->h, groups.data(), (int)groups.size());
 }
 
 extern "C" {
@@ -334,10 +347,8 @@ bg_status_t bs_create(bg_handle_t h, int num_clients, const int* sizes, unsigned
   }
   ok = ok && hipMalloc((void**)&s->pool_base, pool_bytes) == hipSuccess;
   for (int b = 0; b < 2 && ok; ++b)
-    ok = hipMalloc(&s->d_jobs[b], num_clients * sizeof(bg::FillJob)) == hipSuccess &&
-         hipMalloc((void**)&s->d_ptrs[b], 3 * num_clients * sizeof(double*)) == hipSuccess &&
-         hipHostMalloc((void**)&s->h_jobs[b], num_clients * sizeof(bg::FillJob)) == hipSuccess &&
-         hipHostMalloc((void**)&s->h_ptrs[b], 3 * num_clients * sizeof(double*)) == hipSuccess &&
+    ok = hipMalloc((void**)&s->d_tick[b], tick_bytes(num_clients)) == hipSuccess &&
+         hipHostMalloc((void**)&s->h_tick[b], tick_bytes(num_clients)) == hipSuccess &&
          hipMalloc((void**)&s->d_dims[b], 6 * num_clients * sizeof(int)) == hipSuccess &&
          hipHostMalloc((void**)&s->h_dims[b], 6 * num_clients * sizeof(int)) == hipSuccess &&
          hipEventCreate(&s->ev[b]) == hipSuccess;
@@ -542,10 +553,11 @@ bg_status_t bs_run_schedule(bs_server_t s, int n_requests, const double* arrival
     // factor jobs, and the clients grouped by size
     order = sc.batch;
     std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return s->sizes[a] < s->sizes[b]; });
-    bg::FillJob* hj = s->h_jobs[set];
-    const double** hp = s->h_ptrs[set];
-    const double** dp = s->d_ptrs[set];
+                     [&](int a, int b) { return s->sizes[a] > s->sizes[b]; });
+    bg::FillJob* hj = (bg::FillJob*)s->h_tick[set];
+    const double** hp = (const double**)(hj + nb);
+    bg::FillJob* dj = (bg::FillJob*)s->d_tick[set];
+    const double** dp = (const double**)(dj + nb);
     for (int i = 0; i < nb; ++i) {
       const int c = order[i];
       double* f = (double*)(s->pool_base + sc.slot[c]);
@@ -555,14 +567,11 @@ bg_status_t bs_run_schedule(bs_server_t s, int n_requests, const double* arrival
       hp[2 * nb + i] = s->st[s->cur[c] ^ 1][c];
     }
     // the tick's arrays go up, all factors are generated in one launch, then
-    // one batched launch per distinct size, all on the handle's stream
+    // the products, all on the handle's stream
     int max_n = 0;
     for (int i = 0; i < nb; ++i) max_n = std::max(max_n, s->sizes[order[i]]);
-    if (hipMemcpyAsync(s->d_jobs[set], hj, nb * sizeof(bg::FillJob), hipMemcpyHostToDevice,
-                       stream) != hipSuccess ||
-        hipMemcpyAsync((void*)dp, (const void*)hp, 3 * nb * sizeof(double*),
-                       hipMemcpyHostToDevice, stream) != hipSuccess ||
-        bg::launch_fill_factors(s->d_jobs[set], nb, max_n, s->seed, stream) != hipSuccess)
+    if (hipMemcpyAsync(dj, hj, tick_bytes(nb), hipMemcpyHostToDevice, stream) != hipSuccess ||
+        bg::launch_fill_factors(dj, nb, max_n, s->seed, stream) != hipSuccess)
       return BG_STATUS_DEVICE_ERROR;
     if (s->tick_launch == BS_TICK_VBATCHED) {
       // one variable-size launch for the whole tick, planned on the device
@@ -579,16 +588,8 @@ bg_status_t bs_run_schedule(bs_server_t s, int n_requests, const double* arrival
                             dd + 5 * nb, nb, nullptr);
       if (st != BG_STATUS_SUCCESS) return st;
     } else {
-      for (int g0 = 0; g0 < nb;) {
-        int g1 = g0;
-        const int n = s->sizes[order[g0]];
-        while (g1 < nb && s->sizes[order[g1]] == n) ++g1;
-        const bg_status_t st = bg_dgemm_batched(s->h, 'N', 'N', n, n, n, 1.0, dp + g0, n,
-                                                dp + nb + g0, n, 0.0,
-                                                (double* const*)(dp + 2 * nb + g0), n, g1 - g0);
-        if (st != BG_STATUS_SUCCESS) return st;
-        g0 = g1;
-      }
+      const bg_status_t st = multiply(s, order, dp, nb);
+      if (st != BG_STATUS_SUCCESS) return st;
     }
     if (hipEventRecord(s->ev[set], stream) != hipSuccess) return BG_STATUS_DEVICE_ERROR;
     for (int c : sc.batch) {
@@ -617,7 +618,7 @@ bg_status_t bs_run_sweeps(bs_server_t s, int sweeps, int chain, int use_graph,
   std::vector<int> order(nc);
   for (int c = 0; c < nc; ++c) order[c] = c;
   std::stable_sort(order.begin(), order.end(),
-                   [&](int a, int b) { return s->sizes[a] < s->sizes[b]; });
+                   [&](int a, int b) { return s->sizes[a] > s->sizes[b]; });
   // every client takes part in every sweep: each holds a factor of the pool
   s->pool.init(s->pool_bytes, s->need.data(), nc);
   std::vector<double*> fac(nc);
@@ -674,16 +675,8 @@ bg_status_t bs_run_sweeps(bs_server_t s, int sweeps, int chain, int use_graph,
       const double** row = d_ptrs + ((size_t)p * chain + t) * 3 * nc;
       if (bg::launch_fill_sweep(d_jobs, nc, max_n, d_j0, t, s->seed, q) != hipSuccess)
         return BG_STATUS_DEVICE_ERROR;
-      for (int g0 = 0; g0 < nc;) {
-        int g1 = g0;
-        const int n = s->sizes[order[g0]];
-        while (g1 < nc && s->sizes[order[g1]] == n) ++g1;
-        const bg_status_t r = bg_dgemm_batched(s->h, 'N', 'N', n, n, n, 1.0, row + g0, n,
-                                               row + nc + g0, n, 0.0,
-                                               (double* const*)(row + 2 * nc + g0), n, g1 - g0);
-        if (r != BG_STATUS_SUCCESS) return r;
-        g0 = g1;
-      }
+      const bg_status_t r = multiply(s, order, row, nc);
+      if (r != BG_STATUS_SUCCESS) return r;
     }
     return bg::launch_advance(d_j0, nc, chain, q) == hipSuccess ? BG_STATUS_SUCCESS
                                                                  : BG_STATUS_DEVICE_ERROR;

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2203_09353_amd import bgemm, inputs
 from tests.parity import check_instance, op_view, oracle_uniform
 
@@ -231,3 +232,32 @@ def test_huge_leading_dimension(h):
     check_instance(got[0, :, :m].T, ref[0, :, :m].T, op_view(Ac.numpy()[0], k, m, "T"),
                    op_view(B.numpy()[0], k, n, "N"), C.numpy()[0, :, :m].T, 1.0, 0.5,
                    where="huge lda")
+
+
+@pytest.mark.parametrize("ta", "NT")
+@pytest.mark.parametrize("tb", "NT")
+@pytest.mark.parametrize("m,n,k,batch", [(65, 33, 1, 1), (128, 96, 32, 2), (191, 65, 33, 3),
+                                         (64, 129, 97, 2), (130, 257, 31, 40),
+                                         (256, 256, 64, 20)])
+def test_short_batch_tiles_at_their_edges(h, ta, tb, m, n, k, batch):
+    """The two tile shapes of short batches (64 x 32 up to one tile per CU, 64
+    x 64 beyond): within the binary64 bound of the oracle, and the bits of the
+    128 x 64 class."""
+    rows = (m if ta == "N" else k, k if tb == "N" else n, m)
+    cols = (k if ta == "N" else m, n if tb == "N" else k, n)
+    A, B, C = (inputs.uniform_batch(31, s, batch, r, c, r + p)
+               for s, (r, c, p) in enumerate(zip(rows, cols, (1, 0, 3))))
+    Ad, Bd, C1, C2 = A.cuda(), B.cuda(), C.cuda(), C.cuda()
+    h.batched(Ad, Bd, C1, m, n, k, 1.25, -0.5, ta, tb)
+    h.set_uniform_class(2)
+    try:
+        h.batched(Ad, Bd, C2, m, n, k, 1.25, -0.5, ta, tb)
+    finally:
+        h.set_uniform_class(-1)
+    torch.cuda.synchronize()
+    got = C1.cpu().numpy()
+    assert np.array_equal(got.view(np.int64), C2.cpu().numpy().view(np.int64))
+    ref = C.numpy().copy()
+    oracle.gemm_batched(ta, tb, m, n, k, 1.25, A.numpy(), B.numpy(), -0.5, ref)
+    err = np.linalg.norm(got[:, :, :m] - ref[:, :, :m]) / np.linalg.norm(ref[:, :, :m])
+    assert err <= 1e-13

@@ -225,3 +225,33 @@ def test_one_variable_size_launch_per_tick_gives_the_same_states(h):
                 assert p == pw and np.array_equal(S.view(np.int64), W.view(np.int64)), (policy, cl)
         finally:
             srv.close()
+
+
+@pytest.mark.parametrize("extra", [[200, 130], [200, 130] + [65] * 70])
+def test_sizes_sharing_a_launch_give_the_same_states(h, extra):
+    """Nineteen or twenty short size groups (more than one launch holds), on
+    the narrow tiles and, with the 65s, on the wide ones, next to a group that
+    fills the chip by itself (520 clients of 40): the same bits as one
+    variable-size launch per tick, in requests and in captured sweeps."""
+    sizes = list(range(1, 18)) + extra + [40] * 520
+    nc = len(sizes)
+    got = []
+    for mode in (serve.TICK_PER_SIZE, serve.TICK_VBATCHED):
+        srv = serve.Server(h, sizes, seed=43)
+        try:
+            srv.set_tick_launch(mode)
+            srv.run(np.zeros(nc), np.arange(nc), np.full(nc, 3))
+            got.append([srv.state(c)[0] for c in range(nc)])
+        finally:
+            srv.close()
+    srv = serve.Server(h, sizes, seed=43)
+    try:
+        srv.sweeps(3, 1, True)
+        got.append([srv.state(c)[0] for c in range(nc)])
+    finally:
+        srv.close()
+    for c in range(nc):
+        for other in got[1:]:
+            assert np.array_equal(got[0][c].view(np.int64), other[c].view(np.int64)), sizes[c]
+    ref = serving.final_state(43, 18, 130, 3)
+    assert np.linalg.norm(got[0][18] - ref) <= 3e-13 * np.linalg.norm(ref)
