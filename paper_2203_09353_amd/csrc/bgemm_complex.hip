@@ -2,31 +2,35 @@
 // C_i <- alpha op(A_i) op(B_i) + beta C_i with interleaved binary64 (real,
 // imaginary) elements, op = N, T or C (conjugate transpose).
 //
-// The complex product is computed as the real product of embedded operands:
-// with a = op(A)(r, p) and b = op(B)(p, c),
-//     [Re C]   [Re a  -Im a] [Re b]
-//     [Im C] = [Im a   Re a] [Im b]
-// so op(A) becomes a real (2m x 2k) matrix A'' of 2 x 2 blocks and op(B) a
-// real (2k x n) matrix B'' whose rows alternate real and imaginary parts.  The
-// expansion happens while a tile is written to LDS; the contraction is then a
-// real GEMM on the FP64 matrix cores, the same number of multiply-adds as four
-// real products.
+// Four real products per complex one, on the FP64 matrix cores:
+//     Re C += Re a Re b - Im a Im b,   Im C += Re a Im b + Im a Re b
+// with a = op(A)(r, p), b = op(B)(p, c).  An element is one 16-byte unit from
+// global memory to the fragment registers: operand tiles go straight to LDS
+// as they are (no expansion into real and imaginary planes, no staging
+// registers) and one 16-byte LDS read feeds both parts.  Signs, conjugation
+// included, are flipped on the sixteen-row fragments just before use.
 //
-// LDS holds, per step, two planes of the embedded A (the real-part rows
-// [Re a, -Im a] and the imaginary-part rows [Im a, Re a] over pairs of real
-// k) and B's embedded rows [Re b; Im b], all k-major.  One
-// v_mfma_f64_4x4x4_4b_f64 takes a 16-row slab of one plane (lane 16 s + r
-// holds row r at real k s) and four B columns replicated over the four blocks
-// (lane 16 s + 4 b + j holds column j), and yields a 16 x 4 block of the real
-// or of the imaginary parts of C (lane 16 i + 4 b + j holds row 4 b + i,
-// column j).  The two planes go to two accumulators, so the real and the
-// imaginary part of each C element sit in one lane for the complex epilogue.
+// One v_mfma_f64_4x4x4_4b_f64 takes a 16-row slab of op(A) (lane 16 s + r
+// holds row r at k s) and four columns of op(B) replicated over its four
+// blocks (lane 16 s + 4 b + j holds column j), and yields a 16 x 4 block of C's
+// real or imaginary parts (lane 16 i + 4 b + j holds row 4 b + i, column j).
+// The two parts go to two accumulators, so both parts of a C element sit in
+// one lane for the complex epilogue, and a lane group's sixteen rows are 256
+// contiguous bytes of a C column.
 //
-// Tile: 64 x 64 complex C per workgroup, four waves of 32 x 32, eight complex
-// k per step (sixteen real k), double-buffered LDS, loads staged through
-// registers one step ahead.
+// Tile: 64 x 64 complex C per workgroup, four waves of 64 x 16, eight complex k
+// per step, a ring of three LDS stages filled by direct global-to-LDS loads
+// two steps ahead, three workgroups per CU.  What bounds it: the matrix cores
+// (a 256 x 256 x 128 product moves 1.57 MB for 67 MFLOP).
+// Measured: 10,000 x Psi Psi^H of 256 x 128 12.8 -> 10.5 ms (52.5 -> 64 TFLOP/s),
+// 64 of 2048 x 1024 38.6 -> 32.2 ms (68 TFLOP/s), 3,000 x 200 x 90 x 300 conjugated
+// 4.63 -> 3.48, 10,000 x 16 x 16 x 100 0.58 -> 0.15, against register-staged planes
+// of an embedded real operand.  128 x 64 tiles of eight waves ran 11.9 ms (two
+// waves per SIMD), 32 x 16 waves 10.85, two workgroups per CU 11.0.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "bgemm_internal.h"
 
@@ -35,179 +39,243 @@ namespace cplx {
 
 #define AS_GLOBAL __attribute__((address_space(1)))
 #define AS_LDS __attribute__((address_space(3)))
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));  // at any 8-byte boundary
+typedef const AS_GLOBAL double* gcptr;
+typedef AS_LDS d2* uptr;             // a 16-byte unit in LDS: one complex element
+typedef const AS_LDS d2* ucptr;
 
-constexpr int BM = 64, BN = 64, BK = 8, NT = 256;
-constexpr int K2 = 2 * BK;          // real k of a step
-// LDS row strides (doubles) of the A planes and of B's rows: the small pad keeps
-// a stage at 26 KB, so three workgroups fit a CU (measured 52.0 vs 43.5
-// TFLOP/s with a 16-double pad at two per CU)
-#ifndef BG_ZPAD
-#define BG_ZPAD 4
-#endif
-constexpr int SP = BM + BG_ZPAD;
-constexpr int SB = BN + BG_ZPAD;
-constexpr int PLANE = K2 * SP;
-constexpr int STAGE = 2 * PLANE + K2 * SB;
-constexpr int PER = BM * BK / NT;   // complex elements per thread per operand tile
+constexpr int BM = 64, BN = 64, BK = 8, NS = 3, NT = 256, NW = NT / 64;
+constexpr int WM = 64, WN = 16, FP = WM / 16, GQ = WN / 4;
+constexpr int PU = BM * BK / NT;          // units per thread, operand and step
+constexpr int DPT = 2 * PU;               // its direct loads per step
+constexpr int STAGE = (BM + BN) * BK;     // units
+static_assert(BM == WM && BN == NW * WN && BM == BN, "one wave per 16 columns");
 
-struct Z {
-  double re, im;
-};
+// s_waitcnt immediate: vector-memory count vm, LDS/scalar count lgkm, export
+// count unconstrained (gfx9 encoding)
+constexpr int waitcnt_imm(int vm, int lgkm) {
+  return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 15) << 8);
+}
 
-template <int TA, int TB>
-struct Loader {
-  Z a[PER], b[PER];
+__device__ __forceinline__ double flip(double x) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) ^ (1ull << 63));
+}
 
-  // op codes: 0 N, 1 T, 2 C
-  __device__ __forceinline__ void load(const AS_GLOBAL double* A, int64_t lda,
-                                       const AS_GLOBAL double* B, int64_t ldb, int M, int N,
-                                       int K, int m0, int n0, int k0, int tid) {
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int e = tid + it * NT;
-      // A tile element (row w, k q): coalesced along the contiguous index
-      const int w = TA == 0 ? e % BM : e / BK;
-      const int q = TA == 0 ? e / BM : e % BK;
-      const int r = m0 + w, p = k0 + q;
-      Z x{0.0, 0.0};
-      if (r < M && p < K) {
-        const AS_GLOBAL double* s = TA == 0 ? A + 2 * ((int64_t)r + (int64_t)p * lda)
-                                            : A + 2 * ((int64_t)p + (int64_t)r * lda);
-        x.re = s[0];
-        x.im = TA == 2 ? -s[1] : s[1];
-      }
-      a[it] = x;
-      // B tile element (k q, column c)
-      const int q2 = TB == 0 ? e % BK : e / BN;
-      const int c2 = TB == 0 ? e / BK : e % BN;
-      const int p2 = k0 + q2, c = n0 + c2;
-      Z y{0.0, 0.0};
-      if (p2 < K && c < N) {
-        const AS_GLOBAL double* s = TB == 0 ? B + 2 * ((int64_t)p2 + (int64_t)c * ldb)
-                                            : B + 2 * ((int64_t)c + (int64_t)p2 * ldb);
-        y.re = s[0];
-        y.im = TB == 2 ? -s[1] : s[1];
-      }
-      b[it] = y;
-    }
+// An operand tile in LDS: EXT values of its product dimension x BK of k, units
+// in the operand's own order.  MN-contiguous: row k of EXT units (a fragment
+// read's sixteen rows are 256 contiguous bytes).  K-contiguous: rows of BK = 8
+// units, XOR-swizzled by (row / 2) mod 8 so that sixteen rows read at one k
+// fall in sixteen distinct 16-byte bank groups.
+template <int EXT, bool KC>
+struct Tile {
+  static constexpr int UNITS = EXT * BK;
+  __device__ __forceinline__ static int pos(int mn, int k) {
+    return KC ? mn * BK + (k ^ ((mn >> 1) & 7)) : k * EXT + mn;
   }
-
-  __device__ __forceinline__ void store(AS_LDS double* st, int tid) const {
-    AS_LDS double* pre = st;              // rows [Re a, -Im a]
-    AS_LDS double* pim = st + PLANE;      // rows [Im a,  Re a]
-    AS_LDS double* lb = st + 2 * PLANE;
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int e = tid + it * NT;
-      const int w = TA == 0 ? e % BM : e / BK;
-      const int q = TA == 0 ? e / BM : e % BK;
-      pre[(2 * q) * SP + w] = a[it].re;
-      pre[(2 * q + 1) * SP + w] = -a[it].im;
-      pim[(2 * q) * SP + w] = a[it].im;
-      pim[(2 * q + 1) * SP + w] = a[it].re;
-      const int q2 = TB == 0 ? e % BK : e / BN;
-      const int c2 = TB == 0 ? e / BK : e % BN;
-      lb[(2 * q2) * SB + c2] = b[it].re;
-      lb[(2 * q2 + 1) * SB + c2] = b[it].im;
+  // the element that unit u holds
+  __device__ __forceinline__ static void at(int u, int& mn, int& k) {
+    if (KC) {
+      mn = u / BK;
+      k = (u % BK) ^ ((mn >> 1) & 7);
+    } else {
+      mn = u % EXT;
+      k = u / EXT;
     }
   }
 };
 
+// Three waves per SIMD (three workgroups per CU, as many as the LDS holds)
+// need at most 170 registers, which the compiler reaches without a spill (the
+// build checks: a spill would enter the counted waits).
 template <int TA, int TB>
-__global__ __launch_bounds__(NT) void k_zgemm(int M, int N, int K, double ar, double ai,
-                                              const double* const* __restrict__ Ap, int64_t lda,
-                                              const double* const* __restrict__ Bp, int64_t ldb,
-                                              double br, double bi, double* const* __restrict__ Cp,
-                                              int64_t ldc, int tiles_m, int tiles_per_inst,
-                                              int64_t total_tiles, int64_t per_xcd) {
+__global__ __launch_bounds__(NT, 3) void k_uniform_z(
+    int M, int N, int K, double ar, double ai, const double* const* __restrict__ Ap, int64_t lda,
+    const double* const* __restrict__ Bp, int64_t ldb, double br, double bi,
+    double* const* __restrict__ Cp, int64_t ldc, int tiles_m, int tiles_per_inst,
+    int64_t total_tiles, int64_t per_xcd) {
   // the epilogue's complex products round as written (no fused multiply-add)
 #pragma clang fp contract(off)
-  __shared__ double lds_raw[2 * STAGE];
-  AS_LDS double* lds = (AS_LDS double*)lds_raw;
+  using TAt = Tile<BM, TA != 0>;
+  using TBt = Tile<BN, TB == 0>;
+  __shared__ __align__(16) double lds_raw[2 * NS * STAGE];
+  const uptr lds = (uptr)lds_raw;
   const int64_t bid = blockIdx.x;
   const int64_t id = (bid % 8) * per_xcd + bid / 8;   // contiguous tiles per XCD
   if (id >= total_tiles) return;
   const int64_t inst = id / tiles_per_inst;
-  const int t = (int)(id - inst * tiles_per_inst);
-  const int m0 = (t % tiles_m) * BM, n0 = (t / tiles_m) * BN;
-  const AS_GLOBAL double* A = (const AS_GLOBAL double*)Ap[inst];
-  const AS_GLOBAL double* B = (const AS_GLOBAL double*)Bp[inst];
+  const int tt = (int)(id - inst * tiles_per_inst);
+  const int m0 = (tt % tiles_m) * BM, n0 = (tt / tiles_m) * BN;
+  const gcptr A = (gcptr)Ap[inst];
+  const gcptr B = (gcptr)Bp[inst];
   AS_GLOBAL double* C = (AS_GLOBAL double*)Cp[inst];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = (wave & 1) * 32;        // wave's first complex row
-  const int wc = (wave >> 1) * 32;       // wave's first column
-  const int ls = lane >> 4;              // real k within an instruction
-  const int lr = lane & 15, lj = lane & 3;
+  const int wn0 = wave * WN;
+  const int ls = lane >> 4, lr = lane & 15, lj = lane & 3;
 
-  // acc[t][part][g]: slab t (16 rows), part (0 Re, 1 Im), column group g (4)
-  double acc[2][2][8];
+  // This thread's units of a stage, as element offsets from (k = 0) and the
+  // step's advance.  Units outside the matrix re-read the tile's first row or
+  // column: in bounds, every wave issues the same number of direct loads (the
+  // stage waits count them), and their products only reach C elements outside
+  // C.
+  int64_t oa[PU], ob[PU];
+  int ka[PU], kb[PU];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int pt = 0; pt < 2; ++pt)
-#pragma unroll
-      for (int g = 0; g < 8; ++g) acc[t][pt][g] = 0.0;
-
-  Loader<TA, TB> ld;
-  const int nk = (K + BK - 1) / BK;
-  ld.load(A, lda, B, ldb, M, N, K, m0, n0, 0, tid);
-  ld.store(lds, tid);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) ld.load(A, lda, B, ldb, M, N, K, m0, n0, (kt + 1) * BK, tid);
-    const AS_LDS double* pl = lds + cur * STAGE;
-    const AS_LDS double* lb = pl + 2 * PLANE;
-#pragma unroll
-    for (int kk = 0; kk < K2; kk += 4) {
-      double fp[2][2], fq[8];
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int pt = 0; pt < 2; ++pt)
-          fp[t][pt] = pl[pt * PLANE + (kk + ls) * SP + wr + 16 * t + lr];
-#pragma unroll
-      for (int g = 0; g < 8; ++g) fq[g] = lb[(kk + ls) * SB + wc + 4 * g + lj];
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int pt = 0; pt < 2; ++pt)
-#pragma unroll
-          for (int g = 0; g < 8; ++g)
-            acc[t][pt][g] =
-                __builtin_amdgcn_mfma_f64_4x4x4f64(fp[t][pt], fq[g], acc[t][pt][g], 0, 0, 0);
-    }
-    if (kt + 1 < nk) ld.store(lds + (cur ^ 1) * STAGE, tid);
-    __syncthreads();
+  for (int i = 0; i < PU; ++i) {
+    int mn;
+    TAt::at((i * NW + wave) * 64 + lane, mn, ka[i]);
+    const int64_t r = m0 + mn < M ? m0 + mn : m0;
+    oa[i] = TA == 0 ? r + ka[i] * lda : ka[i] + r * lda;
   }
+#pragma unroll
+  for (int i = 0; i < PU; ++i) {
+    int mn;
+    TBt::at((i * NW + wave) * 64 + lane, mn, kb[i]);
+    const int64_t c = n0 + mn < N ? n0 + mn : n0;
+    ob[i] = TB == 0 ? kb[i] + c * ldb : c + kb[i] * ldb;
+  }
+  const int64_t sa = TA == 0 ? BK * lda : BK, sb = TB == 0 ? BK : BK * ldb;
+  const int nk = (K + BK - 1) / BK;
+  const bool tail = K % BK != 0;
 
-  // Epilogue: lane 16 i + 4 b + j holds row wr + 16 t + 4 b + i, column
-  // wc + 4 g + j of slab t, group g (real part in acc[t][0][g], imaginary in
-  // acc[t][1][g]).
-  const bool read_c = !(br == 0.0 && bi == 0.0);
-  const int li = lane >> 4, lb4 = (lane >> 2) & 3;
+  auto issue = [&](int kt, int st) {
+    const uptr la = lds + st * STAGE, lb = la + TAt::UNITS;
+    if (kt == nk - 1 && tail) {
+      // partial in k: through registers, zero beyond K.  Every load is
+      // unconditional (k clamped), and the explicit wait also covers the
+      // direct loads issued before it, whatever this wave's lanes hold.
+      const int k0 = kt * BK;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const int r = m0 + wr + 16 * t + 4 * lb4 + li;
-      const int c = n0 + wc + 4 * g + lj;
-      if (r >= M || c >= N) continue;
-      const double sr = acc[t][0][g], si = acc[t][1][g];
-      double xr = ar * sr - ai * si;
-      double xi = ar * si + ai * sr;
-      AS_GLOBAL double* dst = C + 2 * ((int64_t)r + (int64_t)c * ldc);
-      if (read_c) {
-        const double cr = dst[0], ci = dst[1];
-        const double yr = br * cr - bi * ci;
-        const double yi = br * ci + bi * cr;
-        xr = xr + yr;
-        xi = xi + yi;
+      for (int i = 0; i < PU; ++i) {
+        const int over = k0 + ka[i] >= K ? k0 + ka[i] - (K - 1) : 0;
+        const d2 x = *(const AS_GLOBAL d2u*)(A + 2 * (oa[i] + kt * sa - over * (TA == 0 ? lda : 1)));
+        la[(i * NW + wave) * 64 + lane] = over ? d2{0.0, 0.0} : x;
       }
-      dst[0] = xr;
-      dst[1] = xi;
+#pragma unroll
+      for (int i = 0; i < PU; ++i) {
+        const int over = k0 + kb[i] >= K ? k0 + kb[i] - (K - 1) : 0;
+        const d2 x = *(const AS_GLOBAL d2u*)(B + 2 * (ob[i] + kt * sb - over * (TB == 0 ? 1 : ldb)));
+        lb[(i * NW + wave) * 64 + lane] = over ? d2{0.0, 0.0} : x;
+      }
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    } else {
+#pragma unroll
+      for (int i = 0; i < PU; ++i)
+        __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)(A + 2 * (oa[i] + kt * sa)),
+                                         (AS_LDS void*)(la + (i * NW + wave) * 64), 16, 0, 0);
+#pragma unroll
+      for (int i = 0; i < PU; ++i)
+        __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)(B + 2 * (ob[i] + kt * sb)),
+                                         (AS_LDS void*)(lb + (i * NW + wave) * 64), 16, 0, 0);
     }
+  };
+
+  // acc[t][g]: slab t (16 rows), column group g (4), real and imaginary parts
+  double cr[FP][GQ], ci[FP][GQ];
+#pragma unroll
+  for (int t = 0; t < FP; ++t)
+#pragma unroll
+    for (int g = 0; g < GQ; ++g) cr[t][g] = ci[t][g] = 0.0;
+
+#pragma unroll
+  for (int st = 0; st < NS - 1; ++st)
+    if (st < nk) issue(st, st);
+
+  // Step kt lives in stage kt mod NS.  Its loads are complete once at most the
+  // next step's DPT loads remain (they return in order); the barrier then
+  // publishes every wave's part, and only after it is the stage read one step
+  // earlier refilled.  NPA of the wave's slabs take part (fewer on edge tiles,
+  // none for a wave outside C); every wave issues the same loads and barriers.
+  auto step = [&](int kt, auto stage_c, auto npa_c) {
+    constexpr int st = decltype(stage_c)::value;
+    constexpr int NPA = decltype(npa_c)::value;
+    asm volatile("" ::: "memory");
+    if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_imm(DPT, 0));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_setprio(1);
+    auto refill = [&]() {
+      asm volatile("" ::: "memory");
+      if (kt + NS - 1 < nk) issue(kt + NS - 1, (st + NS - 1) % NS);
+      asm volatile("" ::: "memory");
+    };
+    if constexpr (NPA == 0) refill();
+    const ucptr la = lds + st * STAGE, lb = la + TAt::UNITS;
+    if constexpr (NPA > 0) {
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        d2 p[NPA], q[GQ];
+#pragma unroll
+        for (int t = 0; t < NPA; ++t) p[t] = la[TAt::pos(16 * t + lr, kk + ls)];
+#pragma unroll
+        for (int g = 0; g < GQ; ++g) q[g] = lb[TBt::pos(wn0 + 4 * g + lj, kk + ls)];
+        if (kk == 4) refill();
+#pragma unroll
+        for (int t = 0; t < NPA; ++t) {
+          // signs: Re takes -Im a Im b, or + when exactly one is conjugated;
+          // Im takes Re a Im b negated for conj b, Im a Re b negated for conj a
+          const double pr = p[t].x, pi = p[t].y;
+          const double pir = (TA == 2) == (TB == 2) ? flip(pi) : pi;
+          const double pri = TB == 2 ? flip(pr) : pr;
+          const double pii = TA == 2 ? flip(pi) : pi;
+#pragma unroll
+          for (int g = 0; g < GQ; ++g) {
+            cr[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(pr, q[g].x, cr[t][g], 0, 0, 0);
+            ci[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(pri, q[g].y, ci[t][g], 0, 0, 0);
+          }
+#pragma unroll
+          for (int g = 0; g < GQ; ++g) {
+            cr[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(pir, q[g].y, cr[t][g], 0, 0, 0);
+            ci[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(pii, q[g].x, ci[t][g], 0, 0, 0);
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  auto kloop = [&](auto npa_c) {
+    for (int kt = 0; kt < nk; kt += NS) {
+      step(kt, std::integral_constant<int, 0>{}, npa_c);
+      if (kt + 1 < nk) step(kt + 1, std::integral_constant<int, 1>{}, npa_c);
+      if (kt + 2 < nk) step(kt + 2, std::integral_constant<int, 2>{}, npa_c);
+    }
+  };
+  const int slabs = n0 + wn0 < N ? (M - m0 + 15) / 16 : 0;
+  using std::integral_constant;
+  static_assert(FP == 4, "slab counts below");
+  if (slabs >= 4) kloop(integral_constant<int, 4>{});
+  else if (slabs == 3) kloop(integral_constant<int, 3>{});
+  else if (slabs == 2) kloop(integral_constant<int, 2>{});
+  else if (slabs == 1) kloop(integral_constant<int, 1>{});
+  else kloop(integral_constant<int, 0>{});
+
+  // Epilogue: lane 16 i + 4 b + j holds row 16 t + 4 b + i, column
+  // wn0 + 4 g + j of slab t, group g.
+  const bool read_c = !(br == 0.0 && bi == 0.0);
+  const int row0 = m0 + 4 * ((lane >> 2) & 3) + (lane >> 4);
+#pragma unroll
+  for (int g = 0; g < GQ; ++g) {
+    const int c = n0 + wn0 + 4 * g + lj;
+    d2 cv[FP];
+    if (read_c) {
+#pragma unroll
+      for (int t = 0; t < FP; ++t)
+        if (row0 + 16 * t < M && c < N)
+          cv[t] = *(const AS_GLOBAL d2u*)(C + 2 * (row0 + 16 * t + (int64_t)c * ldc));
+    }
+#pragma unroll
+    for (int t = 0; t < FP; ++t) {
+      if (row0 + 16 * t >= M || c >= N) continue;
+      d2 x{ar * cr[t][g] - ai * ci[t][g], ar * ci[t][g] + ai * cr[t][g]};
+      if (read_c) {
+        x.x = x.x + (br * cv[t].x - bi * cv[t].y);
+        x.y = x.y + (br * cv[t].y + bi * cv[t].x);
+      }
+      *(AS_GLOBAL d2u*)(C + 2 * (row0 + 16 * t + (int64_t)c * ldc)) = x;
+    }
+  }
 }
 
 // C <- beta C (complex), exactly zero when beta == 0 (C not read).
@@ -239,7 +307,7 @@ static hipError_t launch(const ZUniformArgs& a, hipStream_t s) {
   const int64_t total = tpi * a.batch;
   const int64_t per_xcd = (total + 7) / 8;
   if (tpi > INT32_MAX || per_xcd * 8 > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_zgemm<TA, TB>), dim3((unsigned)(per_xcd * 8)), dim3(NT), 0, s, a.m, a.n,
+  hipLaunchKernelGGL((k_uniform_z<TA, TB>), dim3((unsigned)(per_xcd * 8)), dim3(NT), 0, s, a.m, a.n,
                      a.k, a.alpha[0], a.alpha[1], a.A, a.lda, a.B, a.ldb, a.beta[0], a.beta[1],
                      a.C, a.ldc, tiles_m, (int)tpi, total, per_xcd);
   return hipGetLastError();

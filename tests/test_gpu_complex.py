@@ -81,6 +81,16 @@ def test_complex_random(h, m, n, k, ta, tb):
     run_case(h, ta, tb, m, n, k, 0.75 - 1.25j, -0.5 + 2j, seed=2)
 
 
+@pytest.mark.parametrize("m,n,k", [(16, 16, 7), (17, 15, 8), (31, 49, 9), (47, 64, 16),
+                                   (63, 17, 23), (64, 65, 24), (128, 48, 25), (129, 1, 33)])
+@pytest.mark.parametrize("ta,tb", list(itertools.product("NTC", "NTC")))
+def test_complex_tile_edges(h, m, n, k, ta, tb):
+    """Every slab count of a tile and every position of k in the stage ring,
+    with and without a partial last step; exact on Gaussian integers."""
+    run_case(h, ta, tb, m, n, k, 2 - 1j, 1j, pads=(1, 0, 2), seed=3, integer=True)
+    run_case(h, ta, tb, m, n, k, 0.5j, 0.0, pads=(0, 1, 0), seed=4, c_nan=True)
+
+
 @pytest.mark.parametrize("ta,tb", list(itertools.product("NTC", "NTC")))
 def test_complex_gaussian_integers_exact(h, ta, tb):
     run_case(h, ta, tb, 70, 45, 100, 2 - 1j, 1 + 3j, integer=True, pads=(2, 1, 0), seed=3)
