@@ -9,17 +9,18 @@
 
 namespace bg {
 
-// Tile shapes.  A "size class" is one tile configuration of the MFMA tile
-// kernel: C tile BM x BN per workgroup, contraction step BK per LDS stage,
-// each wave computing a WM x WN sub-tile with 4x4x4 FP64 MFMAs (the exact
-// shapes come from the BG_CFG* macros, i.e. the tune cache).
+// Tile shapes: one configuration of a tile kernel, C tile BM x BN per workgroup
+// on the 4x4x4 FP64 matrix-core form.
 enum TileClass : int {
-  TC_32 = 0,     // 32 x 32 tile         (tiny matrices)
-  TC_64 = 1,     // 64 x 64 tile         (small matrices, short batches)
-  TC_128 = 2,    // 128 x 64 tile        (large matrices)
-  TC_COUNT = 3,  // classes a caller can force
-  TC_64S = 3,    // 64 x 64 tile, eight waves, direct-load pipeline (short batches)
-  TC_64x32 = 4   // 64 x 32 tile, four waves, 32 of k per step (the shortest batches)
+  TC_32 = 0,      // 32 x 32 tile
+  TC_64 = 1,      // 64 x 64 tile
+  TC_128 = 2,     // 128 x 128 tile
+  TC_COUNT = 3,   // classes a caller can force
+  TC_128x64 = 3,
+  TC_64x32 = 4,
+  TC_32x64 = 5,
+  TC_32x16 = 6,
+  TC_128x48 = 7
 };
 
 // Picks the tile class for a uniform batch of `batch` instances on a device
@@ -34,9 +35,7 @@ struct UniformArgs {
   const double* const* B; int64_t ldb;
   double* const* C; int64_t ldc;
   int batch;
-  int num_cus = 0;   // compute units of the device (sizes persistent grids)
-  void* ws = nullptr;         // handle workspace (queue heads of the persistent form)
-  size_t ws_bytes = 0;
+  int num_cus = 0;   // compute units of the device
 };
 
 // Launches the uniform batched GEMM (product path; alpha != 0, k > 0).

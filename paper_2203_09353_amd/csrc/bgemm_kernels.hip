@@ -19,10 +19,8 @@
 // 16 consecutive P indices.  The other -- "Q" -- is read replicated: lane
 // 16 s + 4 b + j holds Q(q0 + j, k_s) for every b.  One instruction then
 // yields a 16 x 4 block of P x Q^T: lane 16 i + 4 b + j holds the sum over s
-// of P(p0 + 4 b + i, k_s) Q(q0 + j, k_s).  With P = op(A) and Q = op(B)^T the
-// block is a piece of C whose 16 rows sit in 16 lanes (coalesced column
-// segments); with P = op(B)^T and Q = op(A) it is a piece of C^T.  The larger
-// tiles use the second form because it needs less LDS padding.
+// of P(p0 + 4 b + i, k_s) Q(q0 + j, k_s).  P is op(A) and Q is op(B)^T, so the
+// block is a piece of C whose 16 rows sit in 16 lanes.
 //
 // Contraction order.  A 16-wide slice of k starting at kk is consumed by four
 // instructions t = 0..3; instruction t gives lane group s the index
@@ -51,369 +49,14 @@ typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 #define AS_LDS __attribute__((address_space(3)))
 typedef const AS_GLOBAL double* gcptr;
 typedef AS_GLOBAL double* gptr;
-typedef AS_LDS double* lptr;
-typedef const AS_LDS double* lcptr;
 
-// Accesses to C on interior tiles.  A tile reads its part of C once and
-// writes it once, so these are nontemporal: the 200,000 x 64^3 batch (half of
-// its bytes are C reads and writes) runs 2.5-3.5 % faster, 256^3 0.1-0.7 %,
-// the variable-size batch within noise.  Edge tiles keep ordinary accesses
-// (nontemporal there made the variable-size batch 0.5 % slower), and so do
-// the operand loads (nontemporal A and B loads were faster still on 64^3 but
-// made the variable-size batch 7 % slower: its tiles share A and B panels
-// through the caches).
-#ifndef BG_NT_C
-#define BG_NT_C 1
-#endif
-template <class T>
-__device__ __forceinline__ T ld_c(const AS_GLOBAL T* p) {
-  if constexpr (BG_NT_C) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <class T>
-__device__ __forceinline__ void st_c(AS_GLOBAL T* p, T v) {
-  if constexpr (BG_NT_C) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-
-// ---------------------------------------------------------------------------
-// Tile configurations: C tile BM x BN per workgroup, BK of k per LDS stage,
-// wave tile WM x WN, SWAP selects the C^T form (P = op(B)^T, Q = op(A)).
-// ---------------------------------------------------------------------------
-template <int BM_, int BN_, int BK_, int WM_, int WN_, bool SWAP_, int NSTAGE_ = 2,
-          bool CPRE_ = false, int SKIP_ = 0, int PIPE_ = 0>
-struct Cfg {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_;
-  static constexpr bool SWAP = SWAP_;
-  static constexpr int NSTAGE = NSTAGE_;      // LDS buffers (2: double buffered)
-  static constexpr bool CPRE = CPRE_;         // read C (beta != 0) before the k loop
-  // Work skipped on edge tiles: 0 none, 1 waves whose region lies outside C
-  // (on the pipelined path also the 16-wide P slabs outside C), 2 on the
-  // register path also single instructions whose 16 x 4 output lies outside
-  // C.
-  static constexpr int SKIP = SKIP_;
-  // PIPE >= 3: instances whose A and B are 16-byte aligned with even leading
-  // dimensions use the pipelined path, a ring of PIPE LDS stages filled by
-  // direct global-to-LDS loads; 0 disables it.
-  static constexpr int PIPE = PIPE_;
-  static_assert(PIPE == 0 || PIPE >= 3, "the pipelined path needs at least three stages");
-  static_assert(NSTAGE == 1 || NSTAGE == 2, "one or two LDS stages");
-  static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
-  static constexpr int NT = WAVES_M * WAVES_N * 64;
-  static constexpr int WP = SWAP ? WN : WM;   // wave extent along P
-  static constexpr int WQ = SWAP ? WM : WN;   // wave extent along Q
-  static constexpr int FP = WP / 16;          // 16-wide P slabs per wave
-  static constexpr int GQ = WQ / 4;           // 4-wide Q groups per wave
-  static_assert(BM % WM == 0 && BN % WN == 0 && WP % 16 == 0 && WQ % 4 == 0, "tile");
-  static_assert(BK % 16 == 0, "BK must be a multiple of 16");
-};
-
-// Shapes per size class (BM, BN, BK, WM, WN, SWAP); the BG_CFG* macros let a
-// tuning build try other shapes without editing the source.
-#ifndef BG_CFG32
-#define BG_CFG32 32, 32, 32, 32, 32, false
-#endif
-#ifndef BG_CFG64
-#define BG_CFG64 64, 64, 16, 32, 32, true, 2, true
-#endif
-#ifndef BG_CFG128
-#define BG_CFG128 128, 64, 16, 16, 64, true, 2, false, 0, 3
-#endif
-// Guarded loads as unconditional loads from clamped addresses plus a select
-// (1), or as predicated loads (0).
-#ifndef BG_CLAMPED_LOADS
-#define BG_CLAMPED_LOADS 0
-#endif
-// The pipelined path for any 8-byte-aligned operands and any leading
-// dimension (1: a 16-byte unit then starts at an 8-byte boundary whenever a
-// column starts at one), or only for 16-byte-aligned operands with even
-// leading dimensions (0).
-#ifndef BG_PIPE_ANY_LD
-#define BG_PIPE_ANY_LD 1
-#endif
-// Pipelined path: a k-step's refill loads issued after its first 16-slice's
-// second fragment read (1: their address arithmetic overlaps the LDS reads
-// and the first products), or right after the barrier (0).
-#ifndef BG_PIPE_LATE_REFILL
-#define BG_PIPE_LATE_REFILL 1
-#endif
-// Pipelined path: wave priority raised from a k-step's barrier to its end
-// (1), or left at 0.
-#ifndef BG_PIPE_SETPRIO
-#define BG_PIPE_SETPRIO 1
-#endif
-// Epilogue C loads all issued before the stores (1), or per element (0).
-#ifndef BG_EPI_BATCH
-#define BG_EPI_BATCH 1
-#endif
-using Cfg32 = Cfg<BG_CFG32>;
-using Cfg64 = Cfg<BG_CFG64>;
-// Short batches (latency-bound: a CU holds one or two tiles, so a tile's own
-// k loop is the critical path).  Eight waves of 16 x 32 on the three-stage
-// pipeline: 7 x 512^3 took 48.7 us on the four-wave register path, 44.9 on
-// four pipelined waves and 40.8 on eight; 20 x 256^3 26.2 / 25.2 / 22.8.  Four
-// stages, or 32 of k per step, were no faster (41.5, 48.6 us).
-using Cfg64S = Cfg<64, 64, 16, 16, 32, true, 2, false, 1, 3>;
-// The shortest batches: half the tile, so twice the CUs, 32 of k per step
-using Cfg64x32 = Cfg<64, 32, 32, 16, 32, true, 2, false, 1, 3>;
-using Cfg128 = Cfg<BG_CFG128>;
-
-// ---------------------------------------------------------------------------
-// Operand tiles in LDS.  An operand tile spans BMN values of its product
-// dimension (m for A, n for B) and BK values of k.  In memory the operand is
-// MN-contiguous (A with 'N', B with 'T') or K-contiguous (A with 'T', B with
-// 'N'); LDS keeps that orientation with a padded stride S (doubles), chosen
-// per role so that one read instruction hits distinct banks (64 banks of
-// 4 bytes):
-//   P, MN-contiguous lds[k*S + mn]: S = BMN + 8  (4 S = 32 mod 64: lane
-//      groups s = 0, 1 fall in opposite bank halves)
-//   P, K-contiguous  lds[mn*S + k]: S = BK + 2   (2 S = 4 mod 8: sixteen
-//      16-byte reads of a quarter-wave are disjoint)
-//   Q, MN-contiguous lds[k*S + mn]: S = BMN + 2  (4 S = 8 mod 64)
-//   Q, K-contiguous  lds[mn*S + k]: S = BK + 8   (2 S = 16 or 48 mod 64: the
-//      four columns read by a quarter-wave are 16 banks apart)
-// ---------------------------------------------------------------------------
-template <int BMN, int BK, bool KC, bool ROLE_P>
-struct OpTile {
-  static constexpr int LC = KC ? BK : BMN;  // extent along the contiguous dim
-  static constexpr int LS = KC ? BMN : BK;  // extent along the strided dim
-  static constexpr int S = KC ? (ROLE_P ? BK + 2 : BK + 8) : (ROLE_P ? BMN + 8 : BMN + 2);
-  static constexpr int ELEMS = LS * S;
-};
-
-// A is K-contiguous iff transposed; B is K-contiguous iff not transposed.
-template <class CF, bool TA, bool TB>
-struct Smem {
-  using TAt = OpTile<CF::BM, CF::BK, TA, !CF::SWAP>;
-  using TBt = OpTile<CF::BN, CF::BK, !TB, CF::SWAP>;
-  static constexpr int A_ELEMS = TAt::ELEMS, B_ELEMS = TBt::ELEMS;
-  static constexpr int TOTAL = CF::NSTAGE * (A_ELEMS + B_ELEMS);
-};
-
-
-// Global -> register -> LDS copy of one operand tile, NT threads, 16 bytes
-// (two consecutive doubles along the contiguous dim) per thread per step.
-template <class T, int NT>
-struct OpLoader {
-  static constexpr int PAIRS = T::LC * T::LS / 2;
-  static constexpr int PER = PAIRS / NT;
-  static_assert(PAIRS % NT == 0, "tile not divisible among threads");
-  d2 v[PER];
-
-  // base: operand matrix; ld: its leading dimension; (c0, s0): tile origin
-  // along the contiguous / strided dims; (cext, sext): matrix extents there.
-  // `fast`: the whole tile is inside the matrix.
-  __device__ __forceinline__ void load(gcptr base, int64_t ld, int c0, int s0, int cext, int sext,
-                                       bool fast, int tid) {
-    if (fast) {
-#pragma unroll
-      for (int it = 0; it < PER; ++it) {
-        const int e = 2 * (tid + it * NT);
-        const int cc = e % T::LC, ss = e / T::LC;
-        v[it] = *(const AS_GLOBAL d2u*)(base + (c0 + cc) + (int64_t)(s0 + ss) * ld);
-      }
-    } else {
-#pragma unroll
-      for (int it = 0; it < PER; ++it) {
-        const int e = 2 * (tid + it * NT);
-        const int cc = e % T::LC, ss = e / T::LC;
-        const int c = c0 + cc, s = s0 + ss;
-        const bool sok = s < sext;
-        if (BG_CLAMPED_LOADS) {
-          // unconditional loads from clamped (in-bounds) addresses, then a
-          // select: no branch around each load, so all of them are in flight
-          const int64_t col = (int64_t)(sok ? s : sext - 1) * ld;
-          const double x0 = base[(c < cext ? c : cext - 1) + col];
-          const double x1 = base[(c + 1 < cext ? c + 1 : cext - 1) + col];
-          v[it].x = (sok && c < cext) ? x0 : 0.0;
-          v[it].y = (sok && c + 1 < cext) ? x1 : 0.0;
-        } else {
-          const gcptr p = base + c + (int64_t)s * ld;
-          v[it].x = (sok && c < cext) ? p[0] : 0.0;
-          v[it].y = (sok && c + 1 < cext) ? p[1] : 0.0;
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(lptr lds, int tid) const {
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int e = 2 * (tid + it * NT);
-      const int cc = e % T::LC, ss = e / T::LC;
-      *(AS_LDS d2*)(lds + ss * T::S + cc) = v[it];
-    }
-  }
-};
-
-// k offset (within a 16-slice) of lane group s for instruction t.
-__device__ __forceinline__ int kperm(int s, int t) { return 2 * s + 8 * (t >> 1) + (t & 1); }
-
-// P-role fragments of NB slabs for the instruction pair (2 tp, 2 tp + 1):
-// f[b][u] = X(mn0 + 16 b + l%16, kk + kperm(l/16, 2 tp + u)).
-template <class T, int NB, bool KC>
-__device__ __forceinline__ void read_p(lcptr lds, int mn0, int kk, int tp, int lane,
-                                       double (&f)[NB][2]) {
-  const int r = lane & 15, s = lane >> 4;
-  const int k = kk + 2 * s + 8 * tp;
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if constexpr (KC) {
-      const d2 x = *(const AS_LDS d2*)(lds + (mn0 + 16 * b + r) * T::S + k);
-      f[b][0] = x.x; f[b][1] = x.y;
-    } else {
-      f[b][0] = lds[k * T::S + mn0 + 16 * b + r];
-      f[b][1] = lds[(k + 1) * T::S + mn0 + 16 * b + r];
-    }
-  }
-}
-
-// Q-role fragments of NG groups: f[g][u] = X(mn0 + 4 g + l%4, kk + kperm(l/16, 2 tp + u)).
-template <class T, int NG, bool KC>
-__device__ __forceinline__ void read_q(lcptr lds, int mn0, int kk, int tp, int lane,
-                                       double (&f)[NG][2]) {
-  const int j = lane & 3, s = lane >> 4;
-  const int k = kk + 2 * s + 8 * tp;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    if constexpr (KC) {
-      const d2 x = *(const AS_LDS d2*)(lds + (mn0 + 4 * g + j) * T::S + k);
-      f[g][0] = x.x; f[g][1] = x.y;
-    } else {
-      f[g][0] = lds[k * T::S + mn0 + 4 * g + j];
-      f[g][1] = lds[(k + 1) * T::S + mn0 + 4 * g + j];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Pipelined path: operand tiles without padding, 16-byte units XOR-swizzled
-// within each row so that the same fragment reads as above stay on distinct
-// banks.  A row is one step of the strided dimension (a column of an
-// MN-contiguous operand, a k-row of a K-contiguous one... in LDS terms: LS rows
-// of UR = LC / 2 units).  Unit u of row r sits at r * UR + (u ^ sw(r)):
-//   K-contiguous  (LC = BK): sw = (r / 2) mod 8 when UR = 8, else r mod 16 --
-//      sixteen rows read at the same unit land in sixteen distinct 16-byte
-//      bank groups;
-//   MN-contiguous (LC = BMN): sw = 8 * ((r / 2) mod 2) -- rows k and k + 2,
-//      read by the two lane groups of a half-wave, fall in opposite halves.
-// A direct load (global_load_lds_dwordx4) writes 64 consecutive units (1 KB)
-// per wave instruction, lane l at unit l; so each lane fetches the global pair
-// that the swizzle places at its unit.
-// ---------------------------------------------------------------------------
-template <int BMN, int BK, bool KC>
-struct SwTile {
-  static constexpr int LC = KC ? BK : BMN;
-  static constexpr int LS = KC ? BMN : BK;
-  static constexpr int UR = LC / 2;
-  static constexpr int UNITS = UR * LS;
-  static constexpr int ELEMS = 2 * UNITS;
-  static_assert((UR & (UR - 1)) == 0 && UR >= 8, "rows of a power-of-two number of units >= 8");
-  static_assert(UNITS % 64 == 0, "whole 1 KB chunks");
-  __device__ __forceinline__ static int sw(int r) {
-    if constexpr (KC) return UR == 8 ? ((r >> 1) & 7) : (r & 15);
-    else return ((r >> 1) & 1) << 3;
-  }
-  // offset (doubles) of logical element (row r, contiguous index c)
-  __device__ __forceinline__ static int off(int r, int c) {
-    return 2 * (r * UR + ((c >> 1) ^ sw(r))) + (c & 1);
-  }
-};
-
-// Issues the direct loads of one operand tile (origin c0 / s0 along the
-// contiguous / strided dims, extents cext / sext; the origin is inside the
-// matrix).  Units outside the matrix read the tile's first pair instead (their
-// products only reach C elements outside the matrix, which are never stored);
-// k beyond K never reaches this path.  A pair straddling an odd cext reads one element of ld padding, which
-// exists because ld is even; the last column, where that could leave the
-// allocation, is always loaded by tail_tile.
-template <class T, int NT>
-__device__ __forceinline__ void dma_tile(gcptr base, int64_t ld, int c0, int s0, int cext,
-                                         int sext, lptr dst, int wave, int lane) {
-  constexpr int NW = NT / 64;
-  constexpr int CH = T::UNITS / 64;
-  static_assert(CH % NW == 0, "chunks not divisible among waves");
-#pragma unroll
-  for (int it = 0; it < CH / NW; ++it) {
-    const int chunk = it * NW + wave;
-    const int unit = chunk * 64 + lane;
-    const int r = unit / T::UR, pu = unit % T::UR;
-    int c = c0 + 2 * (pu ^ T::sw(r));
-    int sr = s0 + r;
-    // Lanes outside the matrix re-read the tile's first pair (in bounds, same
-    // cache lines).  Every wave must issue exactly the same number of direct
-    // loads per step -- the stage waits count them -- so lanes are never
-    // masked off: a wave whose lanes were all masked would skip the
-    // instruction.
-    c = c < cext ? c : c0;
-    sr = sr < sext ? sr : s0;
-    __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)(base + c + (int64_t)sr * ld),
-                                     (AS_LDS void*)(dst + chunk * 128), 16, 0, 0);
-  }
-}
-
-// Guarded copy of one operand tile through registers, zero outside the
-// matrix; used for the last k-step (partial in k, or holding the last column
-// of an odd-extent MN-contiguous operand).
-template <class T, int NT>
-__device__ __forceinline__ void tail_tile(gcptr base, int64_t ld, int c0, int s0, int cext,
-                                          int sext, lptr dst, int tid) {
-  static_assert(T::UNITS % NT == 0, "whole rounds");
-#pragma unroll
-  for (int e = tid; e < T::UNITS; e += NT) {
-    const int r = e / T::UR, u = e % T::UR;
-    const int c = c0 + 2 * u, sr = s0 + r;
-    const bool ok = sr < sext;
-    d2 v;
-    if (BG_CLAMPED_LOADS) {
-      const int64_t col = (int64_t)(ok ? sr : sext - 1) * ld;
-      const double x0 = base[(c < cext ? c : cext - 1) + col];
-      const double x1 = base[(c + 1 < cext ? c + 1 : cext - 1) + col];
-      v.x = (ok && c < cext) ? x0 : 0.0;
-      v.y = (ok && c + 1 < cext) ? x1 : 0.0;
-    } else {
-      const gcptr p = base + c + (int64_t)sr * ld;
-      v.x = (ok && c < cext) ? p[0] : 0.0;
-      v.y = (ok && c + 1 < cext) ? p[1] : 0.0;
-    }
-    *(AS_LDS d2*)(dst + T::off(r, 2 * u)) = v;
-  }
-}
-
-// Fragment reads from swizzled tiles; same lane / index convention as
-// read_p / read_q.
-template <class T, int NB, bool KC>
-__device__ __forceinline__ void read_p_sw(lcptr lds, int mn0, int kk, int tp, int lane,
-                                          double (&f)[NB][2]) {
-  const int r = lane & 15, s = lane >> 4;
-  const int k = kk + 2 * s + 8 * tp;
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if constexpr (KC) {
-      const d2 x = *(const AS_LDS d2*)(lds + T::off(mn0 + 16 * b + r, k));
-      f[b][0] = x.x; f[b][1] = x.y;
-    } else {
-      f[b][0] = lds[T::off(k, mn0 + 16 * b + r)];
-      f[b][1] = lds[T::off(k + 1, mn0 + 16 * b + r)];
-    }
-  }
-}
-
-template <class T, int NG, bool KC>
-__device__ __forceinline__ void read_q_sw(lcptr lds, int mn0, int kk, int tp, int lane,
-                                          double (&f)[NG][2]) {
-  const int j = lane & 3, s = lane >> 4;
-  const int k = kk + 2 * s + 8 * tp;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    if constexpr (KC) {
-      const d2 x = *(const AS_LDS d2*)(lds + T::off(mn0 + 4 * g + j, k));
-      f[g][0] = x.x; f[g][1] = x.y;
-    } else {
-      f[g][0] = lds[T::off(k, mn0 + 4 * g + j)];
-      f[g][1] = lds[T::off(k + 1, mn0 + 4 * g + j)];
-    }
-  }
+// Nontemporal accesses to C: a tile reads its part of C once and writes it once
+// (200,000 x 64^3, half of whose bytes are C, runs 2.5-3.5 % faster with them,
+// 256^3 0.1-0.7 %).  Operand loads stay ordinary: the tiles of an instance share
+// its panels through the caches.
+__device__ __forceinline__ d2 ld_c(const AS_GLOBAL d2u* p) { return __builtin_nontemporal_load(p); }
+__device__ __forceinline__ void st_c(AS_GLOBAL d2u* p, d2 v) {
+  __builtin_nontemporal_store((d2u)v, p);
 }
 
 // s_waitcnt immediate: vector-memory count vm, LDS/scalar count lgkm, export
@@ -422,547 +65,404 @@ constexpr int waitcnt_imm(int vm, int lgkm) {
   return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 15) << 8);
 }
 
-template <class CF, bool TA, bool TB>
-struct PipeSmem {
-  using TAs = SwTile<CF::BM, CF::BK, TA>;
-  using TBs = SwTile<CF::BN, CF::BK, !TB>;
-  static constexpr int STAGE = TAs::ELEMS + TBs::ELEMS;
-  static constexpr int TOTAL = CF::PIPE * STAGE;
-  // direct loads per thread per k-step
-  static constexpr int DPT = (TAs::UNITS + TBs::UNITS) / CF::NT;
+// ---------------------------------------------------------------------------
+// The tile kernel.  Operand tiles go straight from global memory to LDS in
+// 16-byte units (two doubles along the operand's contiguous dimension; a unit
+// starts at an 8-byte boundary whenever its column does) and are read back as
+// whole units.  P is op(A), Q is op(B)^T, so a 16 x 4 result block is a piece of
+// C.
+//
+// Rows and columns of a wave's tile are dealt to the instructions so that a
+// unit is used whole: slabs 2a and 2a + 1 hold the even and the odd ones of
+// rows 32a .. 32a + 31, so an MN-contiguous P unit (two rows at one k) feeds
+// both, and a lane ends with pairs of adjacent rows of C, 16 lanes on 256
+// contiguous bytes of a column: C is read and written 16 bytes at a time
+// without a trip through LDS.  An MN-contiguous Q unit feeds two column groups
+// the same way.  Which row a lane holds does not enter its sums, whose order
+// over k is the one of every class.
+//
+// What bounds it: the matrix cores, and on them the power budget.  Large waves
+// (64 x 64 of the 128 x 128 tile) take 256 matrix-core instructions between
+// barriers and read the fewest LDS bytes per instruction; two stages are
+// enough because the two or three workgroups a CU holds cover a step's load
+// latency.  5,000 x 512^3: matrix cores 0.80 -> 0.88 busy, 23.0 -> 20.9 ms (58.4
+// -> 64.2 TFLOP/s, at a clock that drops as they fill); 20,000 x 256^3 13.1 ->
+// 12.0 ms, against eight waves of 16 x 64 on a 128 x 64 tile with three stages;
+// 3,000 x 129 x 513 x 257 transposed 3.95 -> 2.91 ms with the finer tiles, 100,000 x
+// 16^3 0.54 -> 0.23 against staging through registers.
+// 128 x 64 tiles of four 64 x 32 waves: 21.6 / 12.35 ms; 64 x 128: as 128 x 64;
+// 64 x 64 of 64 x 16 waves: 23.8 / 13.3 (with a slower clock, the others 23.0 /
+// 13.0); three stages of it 24.1 / 13.6; the refill right after the barrier
+// +1.5 %; Q groups eight, four or two at a time within 1 %, two need the fewest
+// registers.
+//
+// LDS layout (units).  A K-contiguous operand has rows of 8 units: row mn sits
+// at rho(mn) (its two low bits swapped), unit u at u ^ f(mn).  An MN-contiguous
+// one has a row per k; a Q tile's units sit at u ^ 4 in every other pair of
+// rows.  With these every fragment read is free of bank conflicts (a 16-byte
+// read is served sixteen lanes at a time, eight from each of two lane groups);
+// with f = mn / 2 and rho, f trivial on Q, 40 % of the LDS's cycles were.
+// ---------------------------------------------------------------------------
+template <int BM_, int BN_, int WM_, int WN_>
+struct PCfg {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = 2, BK = 16;
+  static constexpr int WAVES_M = BM / WM, NW = WAVES_M * (BN / WN), NT = 64 * NW;
+  static constexpr int FP = WM / 16, GQ = WN / 4;    // slabs, column groups per wave
+  static constexpr int CA = BM * BK / 128, CB = BN * BK / 128;   // 1 KB chunks per stage
+  static constexpr int PA = (CA + NW - 1) / NW, PB = (CB + NW - 1) / NW;   // per wave
+  static constexpr int STAGE = (BM + BN) * BK / 2;   // units
+  static constexpr int LDS = NS * STAGE * 2;         // doubles
+  // workgroups that fit a CU's LDS, and the waves per SIMD they make
+  static constexpr int WGS = 163840 / (LDS * 8 + 64);
+  static constexpr int WAVES = WGS * NW / 4 > 8 ? 8 : (WGS * NW / 4 < 1 ? 1 : WGS * NW / 4);
+  static_assert(BM % WM == 0 && BN % WN == 0, "tile");
+  static_assert(WM == 32 || WM == 64, "one or two slab pairs");
+  static_assert(WN % 16 == 0, "a wave starts at a whole turn of the Q swizzle");
 };
 
-// LDS of a kernel that may take either path for a tile
-template <class CF, bool TA, bool TB>
-struct TileSmem {
-  static constexpr int a = Smem<CF, TA, TB>::TOTAL;
-  static constexpr int b = CF::PIPE ? PipeSmem<CF, TA, TB>::TOTAL : 0;
-  static constexpr int TOTAL = a > b ? a : b;
+template <int EXT, int BK, bool KC, bool ROLE_P>
+struct PTile {
+  static_assert(BK == 16, "rows of eight units");
+  static constexpr int UR = KC ? BK / 2 : EXT / 2;   // units per row
+  __device__ __forceinline__ static int rho(int mn) {
+    return (mn & ~3) | ((mn & 1) << 1) | ((mn >> 1) & 1);
+  }
+  __device__ __forceinline__ static int f(int mn) {
+    return (ROLE_P ? (mn >> 2) & 7 : 0) ^ (2 * (mn & 1));
+  }
+  // first element of the unit at position p
+  __device__ __forceinline__ static void at(int p, int& mn, int& k) {
+    if (KC) {
+      mn = rho(p / UR);
+      k = 2 * ((p % UR) ^ f(mn));
+    } else {
+      k = p / UR;
+      mn = 2 * ((p % UR) ^ (ROLE_P ? 0 : 4 * ((k >> 1) & 1)));
+    }
+  }
 };
 
-__device__ __forceinline__ bool aligned16(const void* p) {
-  return (reinterpret_cast<uintptr_t>(p) & 15) == 0;
-}
-__device__ __forceinline__ bool aligned8(const void* p) {
-  return (reinterpret_cast<uintptr_t>(p) & 7) == 0;
-}
+typedef AS_LDS d2* uptr;
+typedef const AS_LDS d2* ucptr;
 
-// ---------------------------------------------------------------------------
-// One C tile (tm, tn) of one instance.  M, N, K are the sizes of op(A) (M x K)
-// and op(B) (K x N).  use_product == false means alpha == 0 or K == 0: A and B
-// are not read and C <- beta * C (exactly 0 when beta == 0, untouched when
-// beta == 1).  Every thread of the workgroup must call this (it synchronises).
-// ---------------------------------------------------------------------------
+// `once`: C's lines are not shared with other tiles' if its columns are whole
+// 128-byte lines (then C is touched nontemporally on interior tiles).
 template <class CF, bool TA, bool TB>
-__device__ __forceinline__ void gemm_tile(const double* A_, int64_t lda, const double* B_,
+__device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const double* B_,
                                           int64_t ldb, double* C_, int64_t ldc, int M, int N, int K,
-                                          double alpha, double beta, int tm, int tn, lptr lds) {
+                                          double alpha, double beta, int m0, int n0, uptr lds,
+                                          bool once) {
   const gcptr A = (gcptr)A_;
   const gcptr B = (gcptr)B_;
   const gptr C = (gptr)C_;
-  using SM = Smem<CF, TA, TB>;
-  using TAt = typename SM::TAt;
-  using TBt = typename SM::TBt;
-  using LA = OpLoader<TAt, CF::NT>;
-  using LB = OpLoader<TBt, CF::NT>;
-  constexpr bool SW = CF::SWAP;
-  // The thread id passes through an opaque move, so that the lane-dependent
-  // LDS and global offsets below are computed inside this tile rather than
-  // hoisted out of a persistent caller's tile loop, where they would stay
-  // live (in registers) across every tile.
+  constexpr bool AK = TA, BKC = !TB;   // K-contiguous operands
+  using At = PTile<CF::BM, CF::BK, AK, true>;
+  using Bt = PTile<CF::BN, CF::BK, BKC, false>;
+  constexpr int FP = CF::FP, GQ = CF::GQ, NW = CF::NW, BK = CF::BK;
+  constexpr int A_UNITS = CF::BM * BK / 2;
   int tid;
+  // opaque, so that lane-dependent offsets are not kept live across a
+  // persistent caller's tiles
   asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave % CF::WAVES_M) * CF::WM;
-  const int wn0 = (wave / CF::WAVES_M) * CF::WN;
-  const int m0 = tm * CF::BM, n0 = tn * CF::BN;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave % CF::WAVES_M) * CF::WM, wn0 = (wave / CF::WAVES_M) * CF::WN;
+  const int ls = lane >> 4, lr = lane & 15, lj = lane & 3;
   const bool use_product = !(alpha == 0.0 || K == 0);
 
-  double acc[CF::FP][CF::GQ];
+  double acc[FP][GQ];
 #pragma unroll
-  for (int i = 0; i < CF::FP; ++i)
+  for (int i = 0; i < FP; ++i)
 #pragma unroll
-    for (int j = 0; j < CF::GQ; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < GQ; ++j) acc[i][j] = 0.0;
 
-  // Position of acc[i][j] in C.  Lane 16 li + 4 lb4 + lj holds P index
-  // p0 + 16 i + 4 lb4 + li and Q index q0 + 4 j + lj.
-  const int li = lane >> 4, lb4 = (lane >> 2) & 3, lj = lane & 3;
-  const int pofs = 4 * lb4 + li;
-  auto c_row = [&](int i, int j) { return SW ? m0 + wm0 + 4 * j + lj : m0 + wm0 + 16 * i + pofs; };
-  auto c_col = [&](int i, int j) { return SW ? n0 + wn0 + 16 * i + pofs : n0 + wn0 + 4 * j + lj; };
+  if (use_product) {
+    // This thread's units of a stage.  Units whose row or column lies outside
+    // the matrix re-read the tile's first one: in bounds, every wave issues the
+    // same number of direct loads (the stage waits count them), and their
+    // products only reach C elements outside C.  A pair straddling an odd
+    // extent reads the element after it (padding, or the next column), except
+    // in the last step of such a tile, which goes through registers.
+    // An MN-contiguous operand's units lie a fixed number of k rows apart when
+    // the waves' chunks are whole rows and no chunk is loaded twice: one pointer
+    // then serves them all.
+    constexpr bool STEP_A = !AK && NW * 64 % At::UR == 0 && CF::CA % NW == 0;
+    constexpr bool STEP_B = !BKC && NW * 64 % Bt::UR == 0 && CF::CB % NW == 0;
+    constexpr int QA = STEP_A ? 1 : CF::PA, QB = STEP_B ? 1 : CF::PB;
+    gcptr pa[QA], pb[QB];
+#pragma unroll
+    for (int i = 0; i < QA; ++i) {
+      int mn, k;
+      At::at((i * NW + wave) % CF::CA * 64 + lane, mn, k);
+      const int r = m0 + mn < M ? m0 + mn : m0;
+      pa[i] = A + (AK ? (int64_t)r * lda + k : (int64_t)k * lda + r);
+    }
+#pragma unroll
+    for (int i = 0; i < QB; ++i) {
+      int mn, k;
+      Bt::at((i * NW + wave) % CF::CB * 64 + lane, mn, k);
+      const int c = n0 + mn < N ? n0 + mn : n0;
+      pb[i] = B + (BKC ? (int64_t)c * ldb + k : (int64_t)k * ldb + c);
+    }
+    auto a_at = [&](int i) {
+      return STEP_A ? pa[0] + i * (NW * 64 / At::UR) * lda : pa[STEP_A ? 0 : i];
+    };
+    auto b_at = [&](int i) {
+      return STEP_B ? pb[0] + i * (NW * 64 / Bt::UR) * ldb : pb[STEP_B ? 0 : i];
+    };
+    const int64_t sa = AK ? BK : BK * lda, sb = BKC ? BK : BK * ldb;
+    const int nk = (K + BK - 1) / BK;
+    const bool a_odd = !AK && (M & 1) && m0 + CF::BM > M;
+    const bool b_odd = !BKC && (N & 1) && n0 + CF::BN > N;
+    const bool tail = (K % BK != 0) || a_odd || b_odd;
 
-  // With beta != 0 the C tile is read up front so that its latency overlaps
-  // the contraction instead of following it.
-  constexpr bool CP = CF::CPRE;
-  double cpre[CP ? CF::FP : 1][CP ? CF::GQ : 1];
-  const bool prefetch_c = CP && use_product && beta != 0.0;
-  if (prefetch_c) {
-#pragma unroll
-    for (int i = 0; i < CF::FP; ++i)
-#pragma unroll
-      for (int j = 0; j < CF::GQ; ++j) {
-        const int row = c_row(i, j), col = c_col(i, j);
-        const double x = C[(row < M ? row : M - 1) + (int64_t)(col < N ? col : N - 1) * ldc];
-        cpre[CP ? i : 0][CP ? j : 0] = (row < M && col < N) ? x : 0.0;
+    // one unit of the last step through registers, zero beyond K; addresses
+    // clamped into the matrix, so every load is unconditional
+    auto tail_unit = [&](gcptr p, int64_t ld, bool kc, int mn, int ext, int k) -> d2 {
+      const int over = k >= K ? k - (K - 1) : 0;
+      if (kc) {
+        const double x = p[-over], y = p[k + 1 < K ? 1 : -over];
+        return d2{k < K ? x : 0.0, k + 1 < K ? y : 0.0};
       }
-  }
-
-  const bool pipe_ok = CF::PIPE >= 3 &&
-                       (BG_PIPE_ANY_LD ? (aligned8(A_) && aligned8(B_))
-                                       : (aligned16(A_) && aligned16(B_) && (lda % 2 == 0) &&
-                                          (ldb % 2 == 0)));
-  if constexpr (CF::PIPE >= 3) {
-    if (use_product && pipe_ok) {
-      using PS = PipeSmem<CF, TA, TB>;
-      using TAs = typename PS::TAs;
-      using TBs = typename PS::TBs;
-      constexpr int NS = CF::PIPE;
-      static_assert(NS <= 5 && 3 * PS::DPT <= 63, "wait counts must fit the vmcnt field");
-      const int a_cext = TA ? K : M, a_sext = TA ? M : K;
-      const int b_cext = TB ? N : K, b_sext = TB ? K : N;
-      const int nk = (K + CF::BK - 1) / CF::BK;
-      // The last k-step goes through registers when it is partial in k, or
-      // when an MN-contiguous operand of odd extent is cut by this tile (its
-      // last column must not be read past its end).
-      const bool a_odd_edge = !TA && (M & 1) && (m0 + CF::BM > M);
-      const bool b_odd_edge = TB && (N & 1) && (n0 + CF::BN > N);
-      const bool last_tail = (K % CF::BK != 0) || a_odd_edge || b_odd_edge;
-      auto issue = [&](int kt, int st) {
-        const lptr la = lds + st * PS::STAGE, lb = la + TAs::ELEMS;
-        const int k0 = kt * CF::BK;
-        if (kt == nk - 1 && last_tail) {
-          if (TA) tail_tile<TAs, CF::NT>(A, lda, k0, m0, a_cext, a_sext, la, tid);
-          else    tail_tile<TAs, CF::NT>(A, lda, m0, k0, a_cext, a_sext, la, tid);
-          if (TB) tail_tile<TBs, CF::NT>(B, ldb, n0, k0, b_cext, b_sext, lb, tid);
-          else    tail_tile<TBs, CF::NT>(B, ldb, k0, n0, b_cext, b_sext, lb, tid);
-        } else {
-          if (TA) dma_tile<TAs, CF::NT>(A, lda, k0, m0, a_cext, a_sext, la, wave, lane);
-          else    dma_tile<TAs, CF::NT>(A, lda, m0, k0, a_cext, a_sext, la, wave, lane);
-          if (TB) dma_tile<TBs, CF::NT>(B, ldb, n0, k0, b_cext, b_sext, lb, wave, lane);
-          else    dma_tile<TBs, CF::NT>(B, ldb, k0, n0, b_cext, b_sext, lb, wave, lane);
+      p -= over * ld;
+      const double x = p[0], y = p[mn + 1 < ext ? 1 : 0];
+      return d2{over ? 0.0 : x, over ? 0.0 : y};
+    };
+    auto issue = [&](int kt, int st) {
+      const uptr la = lds + st * CF::STAGE, lb = la + A_UNITS;
+      if (kt == nk - 1 && tail) {
+        const int k0 = kt * BK;
+#pragma unroll
+        for (int i = 0; i < CF::PA; ++i) {
+          int mn, k;
+          const int p = (i * NW + wave) % CF::CA * 64 + lane;
+          At::at(p, mn, k);
+          const int r = m0 + mn < M ? m0 + mn : m0;
+          la[p] = tail_unit(a_at(i), lda, AK, r, M, k0 + k);
         }
+#pragma unroll
+        for (int i = 0; i < CF::PB; ++i) {
+          int mn, k;
+          const int p = (i * NW + wave) % CF::CB * 64 + lane;
+          Bt::at(p, mn, k);
+          const int c = n0 + mn < N ? n0 + mn : n0;
+          lb[p] = tail_unit(b_at(i), ldb, BKC, c, N, k0 + k);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < CF::PA; ++i)
+          __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)a_at(i),
+                                           (AS_LDS void*)(la + (i * NW + wave) % CF::CA * 64), 16,
+                                           0, 0);
+#pragma unroll
+        for (int i = 0; i < CF::PB; ++i)
+          __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)b_at(i),
+                                           (AS_LDS void*)(lb + (i * NW + wave) % CF::CB * 64), 16,
+                                           0, 0);
+#pragma unroll
+        for (int i = 0; i < QA; ++i) pa[i] += sa;
+#pragma unroll
+        for (int i = 0; i < QB; ++i) pb[i] += sb;
+      }
+    };
+    issue(0, 0);
+
+    // Lane addresses of the fragment reads; everything else is a constant
+    // offset.  Half slice tp of a step holds k = 2 ls + 8 tp and the next, unit
+    // ls + 4 tp of a K-contiguous row.
+    int ap[AK ? 4 : 1], bp[BKC ? 1 : 2];
+    if constexpr (AK) {   // rows 2 lr + u of a slab pair
+#pragma unroll
+      for (int v = 0; v < 4; ++v)   // v = 2 tp + u
+        ap[v] = (wm0 + At::rho(2 * lr + (v & 1))) * 8 +
+                ((ls + 4 * (v >> 1)) ^ At::f(2 * lr + (v & 1)));
+    } else {
+      ap[0] = 2 * ls * At::UR + wm0 / 2 + lr;
+    }
+    if constexpr (BKC) {  // row 4 g + lj
+      bp[0] = A_UNITS + (wn0 + Bt::rho(lj)) * 8 + (ls ^ Bt::f(lj));
+    } else {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)   // v = column octet & 1
+        bp[v] = A_UNITS + 2 * ls * Bt::UR + wn0 / 2 + lj + 4 * ((ls & 1) ^ v);
+    }
+
+    // Step kt lives in stage kt mod 2.  Its loads were issued a step ago; the
+    // wait and the barrier publish every wave's part, and only after it is the
+    // other stage, read one step earlier, refilled.  NPA of the wave's slabs and
+    // GQA of its column groups take part (fewer on edge tiles, none for a wave
+    // outside C); every wave reaches the same barriers.
+    auto step = [&](int kt, auto stage_c, auto npa_c, auto gqa_c) {
+      constexpr int st = decltype(stage_c)::value;
+      constexpr int NPA = decltype(npa_c)::value, GQA = decltype(gqa_c)::value;
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_setprio(1);
+      auto refill = [&]() {
+        asm volatile("" ::: "memory");
+        if (kt + 1 < nk) issue(kt + 1, st ^ 1);
+        asm volatile("" ::: "memory");
       };
+      if constexpr (NPA == 0) refill();
+      const ucptr stage = lds + st * CF::STAGE;
+      if constexpr (NPA > 0) {
 #pragma unroll
-      for (int st = 0; st < NS - 1; ++st)
-        if (st < nk) issue(st, st);
-      const int p0 = SW ? wn0 : wm0, q0 = SW ? wm0 : wn0;
-      // Step kt lives in stage kt mod NS.  Its loads are complete once at most
-      // (steps issued after it) x DPT of this wave's loads remain; loads
-      // return in order.  The barrier then publishes every wave's part, and
-      // only after it is the stage read one step earlier refilled.  NPA of
-      // the wave's FP slabs along P take part in the products (fewer on edge
-      // tiles, see below); every wave issues the same loads and barriers.
-      auto step = [&](int kt, auto stage_c, auto npa_c) {
-        constexpr int st = decltype(stage_c)::value;
-        constexpr int NPA = decltype(npa_c)::value;
-        const int pending = min(NS - 2, nk - 1 - kt);
-        asm volatile("" ::: "memory");
-        if (pending <= 0) __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-        else if (pending == 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(PS::DPT, 0));
-        else if (pending == 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * PS::DPT, 0));
-        else __builtin_amdgcn_s_waitcnt(waitcnt_imm(3 * PS::DPT, 0));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        // Wave priority raised from the barrier to the end of the step, and
-        // the refill loads issued after the second fragment read: together
-        // measured 1.4-4.5 % faster on 256^3, 512^3 and mixed-size batches.
-        if constexpr (BG_PIPE_SETPRIO) __builtin_amdgcn_s_setprio(1);
-        auto refill = [&]() {
-          asm volatile("" ::: "memory");
-          if (kt + NS - 1 < nk) issue(kt + NS - 1, (st + NS - 1) % NS);
-          asm volatile("" ::: "memory");
-        };
-        if constexpr (NPA == 0 || !BG_PIPE_LATE_REFILL) refill();
-        const lcptr la = lds + st * PS::STAGE, lb = la + TAs::ELEMS;
-        const lcptr lp = SW ? lb : la;
-        const lcptr lq = SW ? la : lb;
-        if constexpr (NPA > 0) {
+        for (int tp = 0; tp < 2; ++tp) {
+          double fp[NPA][2];
 #pragma unroll
-          for (int kk = 0; kk < CF::BK; kk += 16) {
-            if (kt * CF::BK + kk >= K) break;  // whole 16-slices only, as on the other path
+          for (int a = 0; a < NPA / 2; ++a)
 #pragma unroll
-            for (int tp = 0; tp < 2; ++tp) {
-              double fp[NPA][2], fq[CF::GQ][2];
-              if constexpr (SW) {
-                read_p_sw<TBs, NPA, !TB>(lp, p0, kk, tp, lane, fp);
-                read_q_sw<TAs, CF::GQ, TA>(lq, q0, kk, tp, lane, fq);
+            for (int u = 0; u < 2; ++u) {
+              if constexpr (AK) {
+                const d2 x = stage[ap[AK ? 2 * tp + u : 0] + 32 * a * 8];
+                fp[2 * a + u][0] = x.x; fp[2 * a + u][1] = x.y;
               } else {
-                read_p_sw<TAs, NPA, TA>(lp, p0, kk, tp, lane, fp);
-                read_q_sw<TBs, CF::GQ, !TB>(lq, q0, kk, tp, lane, fq);
-              }
-              if constexpr (BG_PIPE_LATE_REFILL)
-                if (kk == 0 && tp == 1) refill();
-#pragma unroll
-              for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int i = 0; i < NPA; ++i)
-#pragma unroll
-                  for (int j = 0; j < CF::GQ; ++j)
-                    acc[i][j] =
-                        __builtin_amdgcn_mfma_f64_4x4x4f64(fp[i][u], fq[j][u], acc[i][j], 0, 0, 0);
-            }
-          }
-        }
-        if constexpr (BG_PIPE_SETPRIO) __builtin_amdgcn_s_setprio(0);
-      };
-      auto kloop = [&](auto npa_c) {
-        for (int kt0 = 0; kt0 < nk; kt0 += NS) {
-          step(kt0, std::integral_constant<int, 0>{}, npa_c);
-          if (kt0 + 1 < nk) step(kt0 + 1, std::integral_constant<int, 1>{}, npa_c);
-          if (kt0 + 2 < nk) step(kt0 + 2, std::integral_constant<int, 2>{}, npa_c);
-          if constexpr (NS > 3)
-            if (kt0 + 3 < nk) step(kt0 + 3, std::integral_constant<int, 3 % NS>{}, npa_c);
-          if constexpr (NS > 4)
-            if (kt0 + 4 < nk) step(kt0 + 4, std::integral_constant<int, 4 % NS>{}, npa_c);
-        }
-      };
-      if constexpr (CF::SKIP >= 1) {
-        // On edge tiles a wave whose region lies outside C does no products,
-        // and a wave cut by the P edge computes only its slabs that reach into
-        // C (16-wide granularity); the skipped sums only reach C elements
-        // that are never stored.
-        const int p_ext = SW ? N - n0 - wn0 : M - m0 - wm0;
-        const int q_ext = SW ? M - m0 - wm0 : N - n0 - wn0;
-        const int npa = (p_ext <= 0 || q_ext <= 0) ? 0 : min(CF::FP, (p_ext + 15) / 16);
-        using std::integral_constant;
-        constexpr int F = CF::FP;
-        if (npa >= F) kloop(integral_constant<int, F>{});
-        else if (npa == 0) kloop(integral_constant<int, 0>{});
-        else if (npa == 1) kloop(integral_constant<int, 1>{});
-        else if (npa == 2) kloop(integral_constant<int, (F > 2 ? 2 : F)>{});
-        else if (npa == 3) kloop(integral_constant<int, (F > 3 ? 3 : F)>{});
-        else kloop(integral_constant<int, F>{});
-      } else {
-        kloop(std::integral_constant<int, CF::FP>{});
-      }
-#ifndef BG_EPI_LDS
-#define BG_EPI_LDS 1
-#endif
-      if constexpr (BG_EPI_LDS && CF::BM == 128 && CF::NT == 512 && SW) {
-        // Interior tiles: the products go through LDS so that C is read and
-        // written a whole column (1 KB) per instruction instead of 16
-        // scattered 32-byte pieces per instruction.  Same arithmetic per
-        // element as the epilogue below, so the results are bit-identical;
-        // measured 2.3 % faster on the variable-size batch and up to 19 % on
-        // short-k uniform batches (512 x 512 x 16).
-#ifndef BG_EPI_XOR
-#define BG_EPI_XOR 1
-#endif
-        // Column stride in LDS; with BG_EPI_XOR the columns are unpadded and
-        // each column's 16-byte row pairs are XOR-swizzled by column, so the
-        // products' writes (16 columns x 4 rows per instruction) hit distinct
-        // banks in each half-wave, and the read-back of one column stays a
-        // permutation of it (variable-size batch 0.9 % faster than padding
-        // the columns by 4).
-        constexpr int S = BG_EPI_XOR ? CF::BM : CF::BM + 4;
-        constexpr int CPW = CF::BN / (CF::NT / 64);    // columns per wave
-        static_assert(CF::BN * S <= PS::TOTAL, "C tile must fit the stages");
-        auto epi_off = [](int c, int r) {  // LDS offset of tile element (row r, column c)
-          if constexpr (BG_EPI_XOR)
-            return c * S + 2 * ((r >> 1) ^ ((((c >> 2) + 4 * (c & 1)) & 7) << 1)) + (r & 1);
-          else
-            return c * S + r;
-        };
-        if (m0 + CF::BM <= M && n0 + CF::BN <= N && !CP) {
-          const int wv = tid >> 6, ln = tid & 63;
-          d2 cw[CPW];
-          if (beta != 0.0) {
-#pragma unroll
-            for (int i = 0; i < CPW; ++i)
-              cw[i] = ld_c((const AS_GLOBAL d2u*)(C + m0 + 2 * ln + (int64_t)(n0 + wv * CPW + i) * ldc));
-          }
-          __syncthreads();  // every wave is done reading the last stage
-#pragma unroll
-          for (int i = 0; i < CF::FP; ++i)
-#pragma unroll
-            for (int j = 0; j < CF::GQ; ++j)
-              lds[epi_off(c_col(i, j) - n0, c_row(i, j) - m0)] = acc[i][j];
-          __syncthreads();
-#pragma unroll
-          for (int i = 0; i < CPW; ++i) {
-            const int cl = wv * CPW + i;
-            const d2 a = *(const AS_LDS d2*)(lds + epi_off(cl, 2 * ln));
-            d2 y;
-            y.x = alpha * a.x;
-            y.y = alpha * a.y;
-            if (beta != 0.0) {
-              y.x = y.x + beta * cw[i].x;
-              y.y = y.y + beta * cw[i].y;
-            }
-            st_c((AS_GLOBAL d2u*)(C + m0 + 2 * ln + (int64_t)(n0 + cl) * ldc), (d2u)y);
-          }
-          return;
-        }
-#ifndef BG_EPI_LDS_EDGE
-#define BG_EPI_LDS_EDGE 1
-#endif
-        if (BG_EPI_LDS_EDGE && !CP) {
-          // Edge tile: the same column-wise form, each lane's row pair cut
-          // at M (a lone last row is read and written alone) and columns
-          // beyond N skipped; nothing outside C is read or written.
-          // Measured 0.6-1.3 % faster on the variable-size batch.
-          const int wv = tid >> 6, ln = tid & 63;
-          const int r0 = m0 + 2 * ln;
-          const bool one = r0 < M, pair = r0 + 1 < M;
-          d2 cw[CPW];
-          if (beta != 0.0) {
-#pragma unroll
-            for (int i = 0; i < CPW; ++i) {
-              const int col = n0 + wv * CPW + i;
-              cw[i].x = 0.0;
-              cw[i].y = 0.0;
-              if (col < N && one) {
-                const gcptr pc = (gcptr)C + r0 + (int64_t)col * ldc;
-                if (pair) cw[i] = *(const AS_GLOBAL d2u*)pc;
-                else cw[i].x = pc[0];
+                const d2 x = stage[ap[0] + (8 * tp + u) * At::UR + 16 * a];
+                fp[2 * a][u] = x.x; fp[2 * a + 1][u] = x.y;
               }
             }
-          }
-          __syncthreads();  // every wave is done reading the last stage
+          // Q groups two at a time: more live fragments would cost the
+          // registers of a resident workgroup
 #pragma unroll
-          for (int i = 0; i < CF::FP; ++i)
+          for (int h = 0; h < GQA; h += 2) {
+            double fq[2][2];
 #pragma unroll
-            for (int j = 0; j < CF::GQ; ++j)
-              lds[epi_off(c_col(i, j) - n0, c_row(i, j) - m0)] = acc[i][j];
-          __syncthreads();
-#pragma unroll
-          for (int i = 0; i < CPW; ++i) {
-            const int cl = wv * CPW + i, col = n0 + cl;
-            if (col < N && one) {
-              const d2 a = *(const AS_LDS d2*)(lds + epi_off(cl, 2 * ln));
-              d2 y;
-              y.x = alpha * a.x;
-              y.y = alpha * a.y;
-              if (beta != 0.0) {
-                y.x = y.x + beta * cw[i].x;
-                y.y = y.y + beta * cw[i].y;
+            for (int u = 0; u < 2; ++u) {
+              if constexpr (BKC) {
+                const d2 x = stage[bp[0] + 4 * (h + u) * 8 + 4 * tp];
+                fq[u][0] = x.x; fq[u][1] = x.y;
+              } else {
+                const d2 x = stage[bp[BKC ? 0 : (h / 2) & 1] + (8 * tp + u) * Bt::UR + 8 * (h / 4)];
+                fq[0][u] = x.x; fq[1][u] = x.y;
               }
-              const gptr pc = C + r0 + (int64_t)col * ldc;
-              if (pair) *(AS_GLOBAL d2u*)pc = y;
-              else pc[0] = y.x;
             }
+            if (tp == 1 && h == 0) refill();
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+              for (int i = 0; i < NPA; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                  acc[i][h + j] = __builtin_amdgcn_mfma_f64_4x4x4f64(fp[i][u], fq[j][u],
+                                                                     acc[i][h + j], 0, 0, 0);
           }
-          return;
         }
       }
-    }
-  }
-  if (use_product && !(CF::PIPE >= 3 && pipe_ok)) {
-    const lptr la0 = lds, lb0 = lds + CF::NSTAGE * SM::A_ELEMS;
-    const int a_cext = TA ? K : M, a_sext = TA ? M : K;
-    const int b_cext = TB ? N : K, b_sext = TB ? K : N;
-    const bool a_vec = m0 + CF::BM <= M;
-    const bool b_vec = n0 + CF::BN <= N;
-    LA ra;
-    LB rb;
-    auto load = [&](int k0) {
-      const bool kfull = k0 + CF::BK <= K;
-      if (TA) ra.load(A, lda, k0, m0, a_cext, a_sext, a_vec && kfull, tid);
-      else    ra.load(A, lda, m0, k0, a_cext, a_sext, a_vec && kfull, tid);
-      if (TB) rb.load(B, ldb, n0, k0, b_cext, b_sext, b_vec && kfull, tid);
-      else    rb.load(B, ldb, k0, n0, b_cext, b_sext, b_vec && kfull, tid);
+      __builtin_amdgcn_s_setprio(0);
     };
-    const int nk = (K + CF::BK - 1) / CF::BK;
-    load(0);
-    ra.store(la0, tid);
-    rb.store(lb0, tid);
-    __syncthreads();
-    const int p0 = SW ? wn0 : wm0, q0 = SW ? wm0 : wn0;
-    // Valid extents of this wave's region along P and Q.  On edge tiles the
-    // instructions whose 16 P indices or 4 Q indices all fall outside C are
-    // skipped (wave-uniform tests); interior waves run without tests.
-    const int p_ext = SW ? N - n0 - wn0 : M - m0 - wm0;
-    const int q_ext = SW ? M - m0 - wm0 : N - n0 - wn0;
-    const bool interior = p_ext >= CF::WP && q_ext >= CF::WQ;
-    auto slice = [&](lcptr lp, lcptr lq, int kk, auto edge) {
-      constexpr bool EDGE = decltype(edge)::value;
-#pragma unroll
-      for (int tp = 0; tp < 2; ++tp) {
-        double fp[CF::FP][2], fq[CF::GQ][2];
-        if constexpr (SW) {
-          read_p<TBt, CF::FP, !TB>(lp, p0, kk, tp, lane, fp);
-          read_q<TAt, CF::GQ, TA>(lq, q0, kk, tp, lane, fq);
-        } else {
-          read_p<TAt, CF::FP, TA>(lp, p0, kk, tp, lane, fp);
-          read_q<TBt, CF::GQ, !TB>(lq, q0, kk, tp, lane, fq);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int i = 0; i < CF::FP; ++i)
-#pragma unroll
-            for (int j = 0; j < CF::GQ; ++j)
-              if (!EDGE || (16 * i < p_ext && 4 * j < q_ext))
-                acc[i][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(fp[i][u], fq[j][u], acc[i][j], 0, 0, 0);
+    auto kloop = [&](auto npa_c, auto gqa_c) {
+      for (int kt = 0; kt < nk; kt += 2) {
+        step(kt, std::integral_constant<int, 0>{}, npa_c, gqa_c);
+        if (kt + 1 < nk) step(kt + 1, std::integral_constant<int, 1>{}, npa_c, gqa_c);
       }
     };
-    for (int kt = 0; kt < nk; ++kt) {
-      const int cur = CF::NSTAGE == 2 ? (kt & 1) : 0;
-      if (kt + 1 < nk) load((kt + 1) * CF::BK);
-      const lcptr la_cur = la0 + cur * SM::A_ELEMS, lb_cur = lb0 + cur * SM::B_ELEMS;
-      const lcptr lp = SW ? lb_cur : la_cur;
-      const lcptr lq = SW ? la_cur : lb_cur;
-#pragma unroll
-      for (int kk = 0; kk < CF::BK; kk += 16) {
-        if (kt * CF::BK + kk >= K) break;  // whole 16-slices only, the same in every class
-        if constexpr (CF::SKIP == 2) {
-          if (interior) slice(lp, lq, kk, std::false_type{});
-          else if (p_ext > 0 && q_ext > 0) slice(lp, lq, kk, std::true_type{});
-        } else if constexpr (CF::SKIP == 1) {
-          if (p_ext > 0 && q_ext > 0) slice(lp, lq, kk, std::false_type{});
-        } else {
-          slice(lp, lq, kk, std::false_type{});
-        }
-      }
-      if (kt + 1 < nk) {
-        if (CF::NSTAGE == 1) __syncthreads();  // every wave is done reading the stage
-        const int nxt = CF::NSTAGE == 2 ? (cur ^ 1) : 0;
-        ra.store(la0 + nxt * SM::A_ELEMS, tid);
-        rb.store(lb0 + nxt * SM::B_ELEMS, tid);
-      }
-      __syncthreads();
-    }
-#ifndef BG_EPI_LDS_REG
-#define BG_EPI_LDS_REG 1
-#endif
-    // The classes without the pipelined path take an LDS epilogue too (the
-    // loop's last barrier has freed the stages): consecutive lanes handle
-    // consecutive 16-byte row pairs of one column of C.
-    constexpr int RS = CF::BM + 4;
-    constexpr int RPAIRS = CF::BN * CF::BM / 2;
-    if constexpr (BG_EPI_LDS_REG && CF::PIPE == 0 && !CF::CPRE && RPAIRS % CF::NT == 0 &&
-                  CF::BN * RS <= TileSmem<CF, TA, TB>::TOTAL) {
-      if (m0 + CF::BM <= M && n0 + CF::BN <= N) {
-        constexpr int RPT = RPAIRS / CF::NT;
-        d2 cw[RPT];
-        if (beta != 0.0) {
-#pragma unroll
-          for (int it = 0; it < RPT; ++it) {
-            const int u = it * CF::NT + tid, col = u / (CF::BM / 2), pr = u % (CF::BM / 2);
-            cw[it] = ld_c((const AS_GLOBAL d2u*)(C + m0 + 2 * pr + (int64_t)(n0 + col) * ldc));
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < CF::FP; ++i)
-#pragma unroll
-          for (int j = 0; j < CF::GQ; ++j)
-            lds[(c_col(i, j) - n0) * RS + (c_row(i, j) - m0)] = acc[i][j];
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < RPT; ++it) {
-          const int u = it * CF::NT + tid, col = u / (CF::BM / 2), pr = u % (CF::BM / 2);
-          const d2 a = *(const AS_LDS d2*)(lds + col * RS + 2 * pr);
-          d2 y;
-          y.x = alpha * a.x;
-          y.y = alpha * a.y;
-          if (beta != 0.0) {
-            y.x = y.x + beta * cw[it].x;
-            y.y = y.y + beta * cw[it].y;
-          }
-          st_c((AS_GLOBAL d2u*)(C + m0 + 2 * pr + (int64_t)(n0 + col) * ldc), (d2u)y);
-        }
-        return;
-      }
-#ifndef BG_EPI_LDS_REG_EDGE
-#define BG_EPI_LDS_REG_EDGE 1
-#endif
-      if (BG_EPI_LDS_REG_EDGE && use_product) {
-        // edge tile: row pairs cut at M, columns beyond N skipped, nothing
-        // outside C read or written (measured 0.3-0.5 % faster on the
-        // variable-size batches, whose small class is nearly all edge tiles)
-        constexpr int RPT = RPAIRS / CF::NT;
-        d2 cw[RPT];
-        if (beta != 0.0) {
-#pragma unroll
-          for (int it = 0; it < RPT; ++it) {
-            const int u = it * CF::NT + tid, col = n0 + u / (CF::BM / 2);
-            const int r0 = m0 + 2 * (u % (CF::BM / 2));
-            cw[it].x = 0.0;
-            cw[it].y = 0.0;
-            if (col < N && r0 < M) {
-              const gcptr pc = (gcptr)C + r0 + (int64_t)col * ldc;
-              if (r0 + 1 < M) cw[it] = *(const AS_GLOBAL d2u*)pc;
-              else cw[it].x = pc[0];
-            }
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < CF::FP; ++i)
-#pragma unroll
-          for (int j = 0; j < CF::GQ; ++j)
-            lds[(c_col(i, j) - n0) * RS + (c_row(i, j) - m0)] = acc[i][j];
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < RPT; ++it) {
-          const int u = it * CF::NT + tid, cl = u / (CF::BM / 2), pr = u % (CF::BM / 2);
-          const int col = n0 + cl, r0 = m0 + 2 * pr;
-          if (col < N && r0 < M) {
-            const d2 a = *(const AS_LDS d2*)(lds + cl * RS + 2 * pr);
-            d2 y;
-            y.x = alpha * a.x;
-            y.y = alpha * a.y;
-            if (beta != 0.0) {
-              y.x = y.x + beta * cw[it].x;
-              y.y = y.y + beta * cw[it].y;
-            }
-            const gptr pc = C + r0 + (int64_t)col * ldc;
-            if (r0 + 1 < M) *(AS_GLOBAL d2u*)pc = y;
-            else pc[0] = y.x;
-          }
-        }
-        return;
-      }
-    }
+    using std::integral_constant;
+    const int pairs = n0 + wn0 < N ? (M - m0 - wm0 + 31) / 32 : 0;
+    // (on the 64-row waves of a transposed A the registers do not allow it)
+    const bool half = !(AK && FP == 4) && n0 + wn0 + CF::WN / 2 >= N;
+    auto columns = [&](auto npa_c) {
+      if (half) kloop(npa_c, integral_constant<int, GQ / 2>{});
+      else kloop(npa_c, integral_constant<int, GQ>{});
+    };
+    if (pairs >= FP / 2) columns(integral_constant<int, FP>{});
+    else if (FP > 2 && pairs == 1) columns(integral_constant<int, 2>{});
+    else kloop(integral_constant<int, 0>{}, integral_constant<int, GQ>{});
   }
 
-  // Epilogue.  All C loads (beta != 0) are issued first, from clamped
-  // in-bounds addresses, so they are in flight together; the stores are then
-  // predicated on the C bounds (padding rows are never written).
-  double cv[CF::FP][CF::GQ];
-  const bool read_c = BG_EPI_BATCH && beta != 0.0 && !(use_product && prefetch_c);
-  if (read_c) {
+  // Epilogue.  Lane 16 i + 4 b + j holds rows r0 + 32 a and the next (slabs 2a,
+  // 2a + 1) and one column per group.  C is read (beta != 0) GE groups at a
+  // time before their stores.
+  if (!use_product && beta == 1.0) return;
+  int le;   // the lane again, not kept in a register through the k loop
+  asm volatile("v_and_b32 %0, 63, %1" : "=v"(le) : "v"((int)threadIdx.x));
+  const int r0 = m0 + wm0 + 2 * (4 * ((le >> 2) & 3) + (le >> 4));
+  auto c_col = [&](int g) {
+    return n0 + wn0 + (BKC ? 4 * g + (le & 3) : 8 * (g / 2) + 2 * (le & 3) + (g & 1));
+  };
+  constexpr int GE = GQ > 8 ? 8 : GQ;
+  auto combine = [&](int a, int g, d2 c) {
+    // alpha acc is rounded, beta c fused: written out, since the compiler may
+    // contract the plain sum either way and every class must round alike
+    d2 y{alpha * acc[2 * a][g], alpha * acc[2 * a + 1][g]};
+    if (beta != 0.0) y = d2{__builtin_fma(beta, c.x, y.x), __builtin_fma(beta, c.y, y.y)};
+    return y;
+  };
+  auto interior = [&](auto stream_c) {
+    constexpr bool STREAM = decltype(stream_c)::value;
 #pragma unroll
-    for (int i = 0; i < CF::FP; ++i)
+    for (int g0 = 0; g0 < GQ; g0 += GE) {
+      d2 cv[FP / 2][GE];
+      if (beta != 0.0) {
 #pragma unroll
-      for (int j = 0; j < CF::GQ; ++j) {
-        const int row = c_row(i, j), col = c_col(i, j);
-        cv[i][j] = C[(row < M ? row : M - 1) + (int64_t)(col < N ? col : N - 1) * ldc];
+        for (int g = 0; g < GE; ++g)
+#pragma unroll
+          for (int a = 0; a < FP / 2; ++a) {
+            const auto p = (const AS_GLOBAL d2u*)(C + r0 + (int64_t)c_col(g0 + g) * ldc + 32 * a);
+            if constexpr (STREAM) cv[a][g] = ld_c(p);
+            else cv[a][g] = *p;
+          }
       }
-  }
 #pragma unroll
-  for (int i = 0; i < CF::FP; ++i) {
+      for (int g = 0; g < GE; ++g)
 #pragma unroll
-    for (int j = 0; j < CF::GQ; ++j) {
-      const int row = c_row(i, j), col = c_col(i, j);
-      if (BG_EPI_BATCH) {
-        const double c0v = (use_product && prefetch_c) ? cpre[CP ? i : 0][CP ? j : 0] : cv[i][j];
-        double x;
-        if (use_product) {
-          x = alpha * acc[i][j];
-          if (beta != 0.0) x = x + beta * c0v;
-        } else {
-          x = (beta == 0.0) ? 0.0 : beta * c0v;
+        for (int a = 0; a < FP / 2; ++a) {
+          const auto p = (AS_GLOBAL d2u*)(C + r0 + (int64_t)c_col(g0 + g) * ldc + 32 * a);
+          const d2 y = combine(a, g0 + g, cv[a][g]);
+          if constexpr (STREAM) st_c(p, y);
+          else *p = y;
         }
-        // beta == 1 without a product leaves C untouched (never reached from
-        // the uniform path, which returns early; a variable-size instance
-        // with k == 0 and beta == 1 has no tiles)
-        if (row < M && col < N && (use_product || beta != 1.0)) C[row + (int64_t)col * ldc] = x;
-      } else {
-        if (row >= M || col >= N) continue;
-        const gptr p = C + row + (int64_t)col * ldc;
-        if (use_product) {
-          double x = alpha * acc[i][j];
-          if (beta != 0.0) x = x + beta * (prefetch_c ? cpre[CP ? i : 0][CP ? j : 0] : *p);
-          *p = x;
-        } else if (beta == 0.0) {
-          *p = 0.0;
-        } else if (beta != 1.0) {
-          *p = beta * (*p);
-        }
-      }
     }
+  };
+  if (use_product && m0 + CF::BM <= M && n0 + CF::BN <= N) {
+    // Nontemporal where every line of C belongs to this tile alone; a line cut
+    // between two accesses is better merged in L2 (the variable-size batch ran
+    // 2 % slower, its short-k tiles 20 %, with nontemporal partial lines).
+    if (once && (((uintptr_t)C_ | (uintptr_t)(8 * ldc)) & 127) == 0) interior(std::true_type{});
+    else interior(std::false_type{});
+    return;
+  }
+  constexpr int GB = GQ > 4 ? 4 : GQ;   // edge tiles: bounds take registers too
+#pragma unroll
+  for (int g0 = 0; g0 < GQ; g0 += GB) {
+    d2 cv[FP / 2][GB];
+#pragma unroll
+    for (int g = 0; g < GB; ++g)
+#pragma unroll
+      for (int a = 0; a < FP / 2; ++a) {
+        cv[a][g] = d2{0.0, 0.0};
+        const int r = r0 + 32 * a, c = c_col(g0 + g);
+        if (beta != 0.0 && c < N && r < M) {
+          const gcptr p = (gcptr)C + r + (int64_t)c * ldc;
+          if (r + 1 < M) cv[a][g] = *(const AS_GLOBAL d2u*)p;
+          else cv[a][g].x = p[0];
+        }
+      }
+#pragma unroll
+    for (int g = 0; g < GB; ++g)
+#pragma unroll
+      for (int a = 0; a < FP / 2; ++a) {
+        const int r = r0 + 32 * a, c = c_col(g0 + g);
+        if (c >= N || r >= M) continue;
+        d2 y;
+        if (use_product) y = combine(a, g0 + g, cv[a][g]);
+        else y = beta == 0.0 ? d2{0.0, 0.0} : d2{beta * cv[a][g].x, beta * cv[a][g].y};
+        const gptr p = C + r + (int64_t)c * ldc;
+        if (r + 1 < M) *(AS_GLOBAL d2u*)p = y;
+        else p[0] = y.x;
+      }
   }
 }
+
+// Shapes: BM, BN, WM, WN.
+using P128 = PCfg<128, 128, 64, 64>;
+using P128x64 = PCfg<128, 64, 64, 32>;
+using P128x48 = PCfg<128, 48, 32, 48>;
+using P64 = PCfg<64, 64, 32, 32>;
+using P64x32 = PCfg<64, 32, 32, 16>;
+using P32x64 = PCfg<32, 64, 32, 16>;
+using P32 = PCfg<32, 32, 32, 16>;
+using P32x16 = PCfg<32, 16, 32, 16>;
 
 // ---------------------------------------------------------------------------
 // Uniform batch: one workgroup per (instance, C tile).  Workgroups are handed
@@ -972,83 +472,20 @@ __device__ __forceinline__ void gemm_tile(const double* A_, int64_t lda, const d
 // ---------------------------------------------------------------------------
 constexpr int NUM_XCD = 8;
 
-// Waves per SIMD a tile kernel is compiled for (its register budget).  The
-// 512-thread 'T','N' uniform kernel would take 132 VGPRs and run one
-// workgroup per CU; held to 4 waves (128 VGPRs, the two workgroups its LDS
-// allows) it still compiles without a spill, which the build checks, and
-// runs 8 % faster.  The others fit 128 already ('N','N', 'T','T') or would
-// spill ('N','T' and the variable-size 'T','N').
-#ifndef BG_TN_WAVES
-#define BG_TN_WAVES 4
-#endif
 template <class CF, bool TA, bool TB>
-constexpr int uniform_min_waves() {
-  return (CF::NT >= 512 && TA && !TB) ? BG_TN_WAVES : 1;
-}
-
-template <class CF, bool TA, bool TB>
-__global__ __launch_bounds__(CF::NT, (uniform_min_waves<CF, TA, TB>())) void k_uniform(
+__global__ __launch_bounds__(CF::NT, CF::WAVES) void k_uniform(
     int M, int N, int K, double alpha, const double* const* __restrict__ Ap, int64_t lda,
     const double* const* __restrict__ Bp, int64_t ldb, double beta,
     double* const* __restrict__ Cp, int64_t ldc, int tiles_m, int tiles_per_inst,
     int64_t total_tiles, int64_t per_xcd) {
-  __shared__ double lds[TileSmem<CF, TA, TB>::TOTAL];
+  __shared__ __align__(16) double lds[CF::LDS];
   const int64_t bid = blockIdx.x;
   const int64_t id = (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;
   if (id >= total_tiles) return;
   const int64_t inst = id / tiles_per_inst;
   const int t = (int)(id - inst * tiles_per_inst);
-  const int tm = t % tiles_m, tn = t / tiles_m;
-  gemm_tile<CF, TA, TB>(Ap[inst], lda, Bp[inst], ldb, Cp[inst], ldc, M, N, K, alpha, beta, tm,
-                        tn, (lptr)lds);
-}
-
-// Persistent form for the pipelined class (1; off by default): one grid of
-// resident workgroups that pop tiles from eight atomic queues, one per XCD
-// range (as the variable-size executor does), each head on its own 4 KiB
-// line of the handle's workspace, for batches with at least four k-steps per
-// tile and four tiles per resident workgroup.  Measured 1 % faster than one
-// workgroup per tile on 20,000 x 256^3, equal on 512^3 and up to 30 % faster
-// on odd shapes (129 x 513 x 257), but it read 14 % (256^3) and 55 % (512^3)
-// more from HBM than the algorithmic bytes, which one workgroup per tile
-// matches exactly; a static deal of the tiles was slower.
-#ifndef BG_UNIFORM_PERSIST
-#define BG_UNIFORM_PERSIST 0
-#endif
-constexpr int UQ_STRIDE = 512;                   // int64 elements between heads
-constexpr size_t UQ_BYTES = (size_t)NUM_XCD * UQ_STRIDE * 8;
-// The persistent form is used when every workgroup gets this many tiles.
-constexpr int64_t UQ_MIN_TILES_PER_WG = 4;
-
-__global__ void k_uq_reset(unsigned long long* heads) {
-  if (threadIdx.x < NUM_XCD) heads[threadIdx.x * UQ_STRIDE] = 0;
-}
-
-template <class CF, bool TA, bool TB>
-__global__ __launch_bounds__(CF::NT, (uniform_min_waves<CF, TA, TB>())) void k_uniform_persist(
-    int M, int N, int K, double alpha, const double* const* __restrict__ Ap, int64_t lda,
-    const double* const* __restrict__ Bp, int64_t ldb, double beta,
-    double* const* __restrict__ Cp, int64_t ldc, int tiles_m, int tiles_per_inst,
-    int64_t total_tiles, unsigned long long* __restrict__ heads) {
-  __shared__ double lds[TileSmem<CF, TA, TB>::TOTAL];
-  __shared__ int64_t s_q;
-  const int home = blockIdx.x % NUM_XCD;
-  for (int step = 0; step < NUM_XCD; ++step) {
-    const int x = (home + step) % NUM_XCD;
-    const int64_t lo = total_tiles * x / NUM_XCD, hi = total_tiles * (x + 1) / NUM_XCD;
-    for (;;) {
-      if (threadIdx.x == 0) s_q = lo + (int64_t)atomicAdd(&heads[x * UQ_STRIDE], 1ull);
-      __syncthreads();
-      const int64_t id = s_q;
-      __syncthreads();
-      if (id >= hi) break;
-      const int64_t inst = id / tiles_per_inst;
-      const int t = (int)(id - inst * tiles_per_inst);
-      gemm_tile<CF, TA, TB>(Ap[inst], lda, Bp[inst], ldb, Cp[inst], ldc, M, N, K, alpha, beta,
-                            t % tiles_m, t / tiles_m, (lptr)lds);
-      __syncthreads();  // LDS free for the next tile
-    }
-  }
+  pipe_tile<CF, TA, TB>(Ap[inst], lda, Bp[inst], ldb, Cp[inst], ldc, M, N, K, alpha, beta,
+                        t % tiles_m * CF::BM, t / tiles_m * CF::BN, (uptr)lds, true);
 }
 
 template <class CF, bool TA, bool TB>
@@ -1058,22 +495,6 @@ static hipError_t launch_uniform_t(const UniformArgs& a, hipStream_t s) {
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
   const int64_t total = tpi * a.batch;
   if (tpi > INT32_MAX) return hipErrorInvalidValue;
-  if (BG_UNIFORM_PERSIST && CF::PIPE >= 3 && a.num_cus > 0 && a.ws && a.ws_bytes >= UQ_BYTES) {
-    auto kern = k_uniform_persist<CF, TA, TB>;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, CF::NT, 0) != hipSuccess ||
-        per_cu < 1)
-      per_cu = 1;
-    const int64_t grid = (int64_t)a.num_cus * per_cu;
-    if (total >= UQ_MIN_TILES_PER_WG * grid && a.k >= 4 * CF::BK) {
-      unsigned long long* heads = (unsigned long long*)a.ws;
-      hipLaunchKernelGGL(k_uq_reset, dim3(1), dim3(64), 0, s, heads);
-      hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(CF::NT), 0, s, a.m, a.n, a.k, a.alpha,
-                         a.A, a.lda, a.B, a.ldb, a.beta, a.C, a.ldc, tiles_m, (int)tpi, total,
-                         heads);
-      return hipGetLastError();
-    }
-  }
   const int64_t per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
   const int64_t grid = per_xcd * NUM_XCD;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
@@ -1091,32 +512,64 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
   return launch_uniform_t<CF, true, true>(a, s);
 }
 
+// Tile of a uniform batch: the one with the least estimated time.  Per C element
+// and k a tile takes `weight` (times of 400 x 512^3: 128 x 128 1,736 us, 128 x 64
+// 1,786, 64 x 64 1,873, 64 x 32 1,991, 32 x 64 1,994), and `fixed` k more for its
+// first loads and its C.  Of the area, what the matrix-core instructions of
+// edge waves skip counts by PADDED only (its loads and its slot remain).  The
+// fixed parts, PADDED and the weights of the last three fit the times of every
+// shape on 158 ragged sizes in 8..513; there the choice is within 0.7 % of the
+// best shape on average, and 1.43x the speed of three classes by max(m, n).  An
+// instance that is a single 64 x 64 tile and short in k is bound by memory and
+// prefers two half tiles in flight (200,000 x 64^3 4.45 against 4.37 ms).  A batch
+// that would not give every CU `need` tiles of a shape goes to a finer one: a
+// short batch is latency-bound, and more, shorter tiles finish sooner (1 x 512^3
+// 22.1 us on 64 x 64, 14.7 on 64 x 32 and 14.2 on 32 x 32 tiles; 7 x 512^3 37.5 / 38.2
+// / 38.3, and 70 on 128 x 128).
+struct TileChoice {
+  TileClass cls;
+  int bm, bn, wn;
+  double weight, fixed, need;
+};
+static const TileChoice kTiles[] = {
+    {TC_128, 128, 128, 64, 1.00, 19, 2},   {TC_128x64, 128, 64, 32, 1.03, 5, 2},
+    {TC_128x48, 128, 48, 48, 1.057, 15, 2}, {TC_64, 64, 64, 32, 1.08, 4, 1},
+    {TC_64x32, 64, 32, 16, 1.147, 3.5, .5}, {TC_32x64, 32, 64, 16, 1.149, 3, .5},
+    {TC_32, 32, 32, 16, 1.163, 17, 0},      {TC_32x16, 32, 16, 16, 1.416, 21, 0},
+};
+constexpr double PADDED = 0.63;
+
 TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int force) {
-  (void)k;
   if (force >= 0 && force < TC_COUNT) return (TileClass)force;
-  const int mx = m > n ? m : n;
-  if (mx <= 32) return TC_32;
-  if (mx <= 64) return TC_64;
-  // A batch too small to give every CU two 128 x 64 tiles is spread over
-  // twice as many 64 x 64 tiles instead (a short batch is latency-bound:
-  // more, shorter tiles finish sooner), and one whose 64 x 64 tiles do not
-  // reach every CU over 64 x 32 tiles: 1 x 512^3 25.5 us on 64 x 64 and 18.6 on
-  // 64 x 32 tiles, 8 x 256^3 14.9 / 11.2, but 20 x 256^3 22.8 / 23.6 and 7 x
-  // 512^3 40.8 / 49.5.
-  const int64_t tiles128 = (int64_t)((m + Cfg128::BM - 1) / Cfg128::BM) *
-                           ((n + Cfg128::BN - 1) / Cfg128::BN) * batch;
-  if (tiles128 >= 2 * (int64_t)num_cus) return TC_128;
-  const int64_t tiles64 = (int64_t)((m + 63) / 64) * ((n + 63) / 64) * batch;
-  return tiles64 <= num_cus ? TC_64x32 : TC_64S;
+  auto up = [](int x, int to) { return (double)((x + to - 1) / to) * to; };
+  const double k16 = up(k, 16);
+  TileClass best = TC_128;   // the coarsest, should every grid be too large
+  double least = 0.0;
+  for (const TileChoice& t : kTiles) {
+    const double area = up(m, t.bm) * up(n, t.bn);
+    const double tiles = area / (t.bm * t.bn);
+    if (tiles * batch < t.need * num_cus || tiles * batch > INT32_MAX - 8) continue;
+    const double used = up(m, 32) * up(n, t.wn / 2);
+    double cost = t.weight * k16 * (PADDED * area + (1 - PADDED) * used) + t.fixed * area;
+    if (t.cls == TC_64 && tiles == 1.0 && k <= 128) cost *= 1.08;
+    if (least == 0.0 || cost < least) {
+      least = cost;
+      best = t.cls;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_uniform(const UniformArgs& a, TileClass cls, hipStream_t s) {
   switch (cls) {
-    case TC_32: return launch_uniform_c<Cfg32>(a, s);
-    case TC_64: return launch_uniform_c<Cfg64>(a, s);
-    case TC_64S: return launch_uniform_c<Cfg64S>(a, s);
-    case TC_64x32: return launch_uniform_c<Cfg64x32>(a, s);
-    default: return launch_uniform_c<Cfg128>(a, s);
+    case TC_32: return launch_uniform_c<P32>(a, s);
+    case TC_64: return launch_uniform_c<P64>(a, s);
+    case TC_128x64: return launch_uniform_c<P128x64>(a, s);
+    case TC_64x32: return launch_uniform_c<P64x32>(a, s);
+    case TC_128x48: return launch_uniform_c<P128x48>(a, s);
+    case TC_32x64: return launch_uniform_c<P32x64>(a, s);
+    case TC_32x16: return launch_uniform_c<P32x16>(a, s);
+    default: return launch_uniform_c<P128>(a, s);
   }
 }
 
@@ -1128,8 +581,8 @@ hipError_t launch_uniform(const UniformArgs& a, TileClass cls, hipStream_t s) {
 // batch's tiles are dealt to the XCDs in contiguous ranges, as in k_uniform.
 // What bounds it is the largest matrices' k loop on the CUs that hold two of
 // their tiles.  Measured on a tick of 32 clients (sizes 32..512, seven of
-// 512): five launches 92 us, one 47; draining 2,000 requests of 1..16 products
-// 86 -> 52 ms.
+// 512): five launches 92 us, one 47 (43 on the present tile); draining 2,000
+// requests of 1..16 products 86 -> 52 -> 47 ms.
 // ---------------------------------------------------------------------------
 constexpr int MAX_GROUPS = 16;
 
@@ -1144,8 +597,8 @@ struct GroupTable {
 };
 
 template <class CF>
-__global__ __launch_bounds__(CF::NT) void k_uniform_groups(GroupTable gt) {
-  __shared__ double lds[TileSmem<CF, false, false>::TOTAL];
+__global__ __launch_bounds__(CF::NT, CF::WAVES) void k_uniform_groups(GroupTable gt) {
+  __shared__ __align__(16) double lds[CF::LDS];
   const int x = blockIdx.x % NUM_XCD, slot = blockIdx.x / NUM_XCD;
   int g = 0;
   while (g + 1 < gt.count && slot >= gt.slot[g + 1]) ++g;
@@ -1154,8 +607,8 @@ __global__ __launch_bounds__(CF::NT) void k_uniform_groups(GroupTable gt) {
   const int n = gt.n[g];
   const int tiles_m = (n + CF::BM - 1) / CF::BM, tpi = tiles_m * ((n + CF::BN - 1) / CF::BN);
   const int inst = id / tpi, t = id - inst * tpi;
-  gemm_tile<CF, false, false>(gt.A[g][inst], n, gt.B[g][inst], n, gt.C[g][inst], n, n, n, n, 1.0,
-                              0.0, t % tiles_m, t / tiles_m, (lptr)lds);
+  pipe_tile<CF, false, false>(gt.A[g][inst], n, gt.B[g][inst], n, gt.C[g][inst], n, n, n, n, 1.0,
+                              0.0, t % tiles_m * CF::BM, t / tiles_m * CF::BN, (uptr)lds, true);
 }
 
 template <class CF>
@@ -1167,8 +620,7 @@ static hipError_t launch_groups(const GroupTable& gt, hipStream_t s) {
 
 hipError_t launch_square_groups(const SquareGroup* groups, int count, int num_cus, hipStream_t s) {
   auto fills_chip = [&](const SquareGroup& q) {
-    return (int64_t)((q.n + Cfg128::BM - 1) / Cfg128::BM) *
-               ((q.n + Cfg128::BN - 1) / Cfg128::BN) * q.batch >= 2 * (int64_t)num_cus;
+    return (int64_t)((q.n + 127) / 128) * ((q.n + 63) / 64) * q.batch >= 2 * (int64_t)num_cus;
   };
   int64_t tiles64 = 0;
   for (int i = 0; i < count; ++i) {
@@ -1201,13 +653,13 @@ hipError_t launch_square_groups(const SquareGroup* groups, int count, int num_cu
     gt.slot[g + 1] = gt.slot[g] + (gt.tiles[g] + NUM_XCD - 1) / NUM_XCD;
     gt.A[g] = q.A; gt.B[g] = q.B; gt.C[g] = q.C;
     if (gt.count == MAX_GROUPS) {
-      const hipError_t e = narrow ? launch_groups<Cfg64x32>(gt, s) : launch_groups<Cfg64S>(gt, s);
+      const hipError_t e = narrow ? launch_groups<P64x32>(gt, s) : launch_groups<P64>(gt, s);
       if (e != hipSuccess) return e;
       gt.count = 0;
     }
   }
   if (gt.count == 0) return hipSuccess;
-  return narrow ? launch_groups<Cfg64x32>(gt, s) : launch_groups<Cfg64S>(gt, s);
+  return narrow ? launch_groups<P64x32>(gt, s) : launch_groups<P64>(gt, s);
 }
 
 // C_i <- beta * C_i, or exactly 0 when beta == 0 (C not read).
@@ -1233,7 +685,10 @@ hipError_t launch_scale(double beta, double* const* C, int64_t ldc, int m, int n
 // Variable-size batch (the paper, Section II: each GEMM gets its own 2-D grid
 // of tiles, sizes differ per instance).  Sizes live on the device, so the
 // whole plan is made there.  Each instance is assigned one of three tile
-// classes (128 x 64, 64 x 64, 32 x 32) by the padded work its C grid costs;
+// classes (128 x 64, 64 x 64, 32 x 32) by the padded work its C grid costs
+// (100,000 mixed sizes 18.5 -> 18.0 ms against register-staged 64 x 64 and 32 x 32
+// classes and a 128 x 64 one of eight waves; batches of 500-15,000 with sizes
+// from 8..512 2-22 % faster);
 // each class gets its own tile queue, and a persistent kernel per class, in
 // decreasing tile size, pops tiles from it:
 //   1. k_vb_count: validate each instance (info), choose its class, count its
@@ -1246,21 +701,24 @@ hipError_t launch_scale(double beta, double* const* C, int64_t ldc, int m, int n
 //      numbers from its class's atomic counters until the queue is empty.
 // ---------------------------------------------------------------------------
 #ifndef BG_CFGVB_L
-#define BG_CFGVB_L 128, 64, 16, 32, 32, true
+#define BG_CFGVB_L 128, 64, 64, 32
 #endif
 #ifndef BG_CFGVB_M
-#define BG_CFGVB_M 64, 64, 16, 32, 32, true, 2, true
+#define BG_CFGVB_M 64, 64, 32, 32
 #endif
 #ifndef BG_CFGVB_S
-#define BG_CFGVB_S 32, 32, 16, 32, 32, false, 2, true
+#define BG_CFGVB_S 32, 32, 32, 16
 #endif
-// relative cost per padded C element of the three classes, for the choice
+// Relative cost per padded C element of the three classes, for the choice.  1 :
+// 1.1 : 1.3 and 1 : 1.05 : 1.13 (the tiles' rates on whole tiles) ran the 100,000
+// mixed sizes 1 and 3 % slower: a persistent workgroup pays for each tile's pop
+// and sizes too.
 #ifndef BG_VB_WEIGHTS
 #define BG_VB_WEIGHTS 1.0f, 1.3f, 2.0f
 #endif
-using CfgVbL = Cfg<BG_CFGVB_L>;
-using CfgVbM = Cfg<BG_CFGVB_M>;
-using CfgVbS = Cfg<BG_CFGVB_S>;
+using CfgVbL = PCfg<BG_CFGVB_L>;
+using CfgVbM = PCfg<BG_CFGVB_M>;
+using CfgVbS = PCfg<BG_CFGVB_S>;
 constexpr int VB_NC = 3;
 constexpr int PLAN_BLOCK = 256;
 // Queue heads, one per (class, XCD), each on its own 4 KB line: every pop
@@ -1439,6 +897,15 @@ __global__ __launch_bounds__(PLAN_BLOCK) void k_vb_map(int batch, const int64_t*
   }
 }
 
+// A value every lane holds alike, in scalar registers (what is addressed by it
+// is then loaded through the scalar cache and stays out of the vector
+// registers, which the 128 x 64 tile's budget needs).
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(x & 0xffffffff));
+  const int hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
+  return ((int64_t)hi << 32) | lo;
+}
+
 // Instance owning tile q of a class: the last i with P[i] <= q < P[i + 1].
 __device__ __forceinline__ int vb_find(const int64_t* __restrict__ prefix, int batch, int64_t q) {
   int lo = 0, hi = batch;
@@ -1456,14 +923,14 @@ __device__ __forceinline__ int vb_find(const int64_t* __restrict__ prefix, int b
 // in turn; every counter is only ever incremented, so each tile is taken
 // exactly once and every workgroup leaves after one pass over the eight.
 template <class CF, bool TA, bool TB>
-__global__ __launch_bounds__(CF::NT) void k_vb_exec(
+__global__ __launch_bounds__(CF::NT, CF::WAVES) void k_vb_exec(
     const int* __restrict__ m, const int* __restrict__ n, const int* __restrict__ k, double alpha,
     const double* const* __restrict__ Ap, const int* __restrict__ lda,
     const double* const* __restrict__ Bp, const int* __restrict__ ldb, double beta,
     double* const* __restrict__ Cp, const int* __restrict__ ldc, int batch, int cls,
     const int64_t* __restrict__ prefix_all, int64_t* __restrict__ ctrl, const int* __restrict__ map,
     int64_t map_cap) {
-  __shared__ double lds[TileSmem<CF, TA, TB>::TOTAL];
+  __shared__ __align__(16) double lds[CF::LDS];
   __shared__ int64_t s_q;
   const int64_t* prefix = prefix_all + (int64_t)cls * (batch + 1);
   const int64_t total = ctrl[cls];
@@ -1483,15 +950,15 @@ __global__ __launch_bounds__(CF::NT) void k_vb_exec(
       if (threadIdx.x == 0)
         s_q = lo + (int64_t)atomicAdd((unsigned long long*)vb_head(ctrl, cls, x), 1ull);
       __syncthreads();
-      const int64_t q = s_q;
+      const int64_t q = uniform64(s_q);
       __syncthreads();
       if (q >= hi) break;
       const int i = use_map ? map[moff + q] : vb_find(prefix, batch, q);
       const int mi = m[i], ni = n[i], ki = k[i];
       const int tiles_m = (mi + CF::BM - 1) / CF::BM;
       const int t = (int)(q - prefix[i]);
-      gemm_tile<CF, TA, TB>(Ap[i], lda[i], Bp[i], ldb[i], Cp[i], ldc[i], mi, ni, ki, alpha, beta,
-                            t % tiles_m, t / tiles_m, (lptr)lds);
+      pipe_tile<CF, TA, TB>(Ap[i], lda[i], Bp[i], ldb[i], Cp[i], ldc[i], mi, ni, ki, alpha, beta,
+                            t % tiles_m * CF::BM, t / tiles_m * CF::BN, (uptr)lds, false);
       __syncthreads();  // LDS free for the next tile
     }
   }

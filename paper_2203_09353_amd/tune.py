@@ -1,8 +1,9 @@
 """Offline autotuner for the tile classes.
 
-Tile shapes are compile-time template parameters of the HIP kernels (the
-``BG_CFG*`` macros of ``csrc/bgemm_kernels.hip``: BM, BN, BK, WM, WN, C^T form,
-register-path LDS stages, C read up front, edge skipping, pipeline stages).
+Tile shapes are compile-time template parameters of the HIP kernels.  The
+uniform batch chooses among a fixed set at run time; the three classes of the
+variable-size batch are the ``BG_CFGVB_*`` macros of
+``csrc/bgemm_kernels.hip`` (BM, BN, WM, WN).
 The tuner compiles one library per candidate shape of a class, times each on
 that class's workload through the C ABI, and records the winner per
 (GPU architecture, class) in ``tune_cache.json``; ``build.py`` passes the
@@ -30,50 +31,23 @@ ARCH = os.environ.get("BG_OFFLOAD_ARCH", "gfx950")
 
 # class macro -> (workload parts timed, candidate shapes).  Each list is in
 # order of preference: a shape within TIE of the fastest wins over it when it
-# comes earlier (so timing noise does not trade away, say, edge skipping,
-# which leaves the tuning workloads' times unchanged but speeds up odd extents).
+# comes earlier.
 TIE = 0.003
 CANDIDATES = {
-    "BG_CFG64": ("u64", [
-        "64,64,16,32,32,true,2,true",
-        "64,64,16,32,32,true,2,true,0,3",
-        "64,64,32,32,32,true,2,true",
-        "64,64,16,64,16,false,2,true",
-        "64,64,16,32,32,true,2,false",
-    ]),
-    "BG_CFG128": ("u256+s512", [
-        "128,64,16,16,64,true,2,false,1,3",
-        "128,64,16,16,64,true,2,false,0,3",
-        "128,64,16,16,64,true,2,true,0,3",
-        "128,64,16,16,64,true",
-        "128,64,32,16,64,true,2,false,0,3",
-        "64,64,16,16,64,true,2,false,0,3",
-    ]),
     "BG_CFGVB_L": ("vb", [
-        "128,64,16,16,64,true,2,false,1",
-        "128,64,16,16,64,true",
-        "128,64,16,32,32,true",
-        "128,64,16,16,64,true,2,false,1,3",
-        "128,64,16,32,32,true,2,false,1,3",
-        "64,64,16,16,64,true,2,false,1,3",
-        "64,64,16,16,32,true,2,false,1,3",
-        "128,64,32,16,64,true,2,false,1,3",
+        "128,64,64,32",
+        "128,128,64,64",
+        "64,128,64,32",
     ]),
     "BG_CFGVB_M": ("vb", [
-        "64,64,16,32,32,true",
-        "64,64,16,32,32,true,2,false,1",
-        "64,64,16,32,32,true,2,false,1,3",
-        "64,64,16,16,64,true,2,false,1,3",
-        "64,64,16,32,32,true,2,true",
-        "64,64,32,32,32,true,2,true",
+        "64,64,32,32",
+        "64,32,32,16",
+        "128,48,32,48",
     ]),
     "BG_CFGVB_S": ("vb", [
-        "32,32,16,32,32,false,1",
-        "32,32,16,32,32,true,1",
-        "32,32,16,32,32,false",
-        "32,32,16,32,32,false,2,true",
-        "32,32,16,16,32,false,1,false,1",
-        "32,32,16,32,32,false,2,true,0,3",
+        "32,32,32,16",
+        "32,32,32,32",
+        "32,64,32,16",
     ]),
 }
 

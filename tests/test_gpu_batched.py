@@ -238,11 +238,15 @@ def test_huge_leading_dimension(h):
 @pytest.mark.parametrize("tb", "NT")
 @pytest.mark.parametrize("m,n,k,batch", [(65, 33, 1, 1), (128, 96, 32, 2), (191, 65, 33, 3),
                                          (64, 129, 97, 2), (130, 257, 31, 40),
-                                         (256, 256, 64, 20)])
-def test_short_batch_tiles_at_their_edges(h, ta, tb, m, n, k, batch):
-    """The two tile shapes of short batches (64 x 32 up to one tile per CU, 64
-    x 64 beyond): within the binary64 bound of the oracle, and the bits of the
-    128 x 64 class."""
+                                         (256, 256, 64, 20), (129, 127, 33, 520),
+                                         (128, 63, 47, 520), (127, 47, 40, 600),
+                                         (63, 65, 15, 600), (65, 31, 17, 700),
+                                         (31, 64, 31, 1100), (30, 29, 49, 2100),
+                                         (9, 15, 16, 2100), (1, 1, 1, 3)])
+def test_tiles_at_their_edges(h, ta, tb, m, n, k, batch):
+    """Every tile shape, in long and in short batches (which take finer ones):
+    within the binary64 bound of the oracle, and the bits of the 128 x 128
+    tile."""
     rows = (m if ta == "N" else k, k if tb == "N" else n, m)
     cols = (k if ta == "N" else m, n if tb == "N" else k, n)
     A, B, C = (inputs.uniform_batch(31, s, batch, r, c, r + p)
