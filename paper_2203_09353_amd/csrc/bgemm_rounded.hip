@@ -28,6 +28,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "bgemm_internal.h"
 
 namespace bg {
@@ -228,31 +230,41 @@ __global__ __launch_bounds__(NT, NT / 128) void k_rounded(
     __syncthreads();
   }
 
-  // epilogue: lane holds C(m0 + wm0 + 16 i + li, n0 + wn0 + 16 j + 4 lg + v)
+  // epilogue: lane holds C(m0 + wm0 + 16 i + li, n0 + wn0 + 16 j + 4 lg + v).
+  // Nontemporal only where the columns are whole 128-byte lines: two tiles, or
+  // two columns, may share a line otherwise, and its parts reach memory one by
+  // one (432 x 450 x 91 x 11 in binary32: 93 us so, 42 us with ordinary stores).
+  const auto write = [&](auto lines) {
 #pragma unroll
-  for (int i = 0; i < FA; ++i) {
-    const int row = m0 + wm0 + 16 * i + li;
-    double cv[FB][4];
-    if (beta != 0.0) {
+    for (int i = 0; i < FA; ++i) {
+      const int row = m0 + wm0 + 16 * i + li;
+      double cv[FB][4];
+      if (beta != 0.0) {
+#pragma unroll
+        for (int j = 0; j < FB; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int col = n0 + wn0 + 16 * j + 4 * lg + v;
+            cv[j][v] = C[min(row, M - 1) + (int64_t)min(col, N - 1) * ldc];
+          }
+      }
 #pragma unroll
       for (int j = 0; j < FB; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int col = n0 + wn0 + 16 * j + 4 * lg + v;
-          cv[j][v] = C[min(row, M - 1) + (int64_t)min(col, N - 1) * ldc];
+          double x = alpha * (double)acc[i][j][v];
+          if (beta != 0.0) x = x + beta * cv[j][v];
+          const gptr p = C + row + (int64_t)col * ldc;
+          if (row < M && col < N) {
+            if constexpr (lines) __builtin_nontemporal_store(x, p);
+            else *p = x;
+          }
         }
     }
-#pragma unroll
-    for (int j = 0; j < FB; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int col = n0 + wn0 + 16 * j + 4 * lg + v;
-        double x = alpha * (double)acc[i][j][v];
-        if (beta != 0.0) x = x + beta * cv[j][v];
-        if (row < M && col < N) 
-          __builtin_nontemporal_store(x, C + row + (int64_t)col * ldc);
-      }
-  }
+  };
+  if ((((uintptr_t)C | (uintptr_t)(8 * ldc)) & 127) == 0) write(std::true_type{});
+  else write(std::false_type{});
 }
 
 template <bool F32, int BM, int BN, int NT>
