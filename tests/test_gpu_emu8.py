@@ -169,3 +169,22 @@ def test_i8_scalar_rules_and_errors(h):
     with pytest.raises(bgemm.BgemmError) as e:
         h.batched_mode("i8emu", Ad, Bd, Cd, 20, 30, 20, slices=3, transa="T")
     assert e.value.status == 2
+
+
+@pytest.mark.parametrize("s", [5, 7, 8])
+@pytest.mark.parametrize("pad", [0, 14])      # C's columns: part lines, whole 128-byte lines
+def test_i8_several_tiles_per_workgroup(h, s, pad):
+    # two tiles an instance and more of them than two workgroups a CU, so that
+    # the first step of a tile is loaded during the tile before; among them
+    # rows and columns down to the smallest subnormals, whose scale is split
+    m, n, k = 130, 5, 70
+    batch = torch.cuda.get_device_properties(0).multi_processor_count + 20
+    A, B, C = _operands(29, m, n, k, batch, (0, 0, pad), 0)
+    A[::3, :, 1::7] *= 2.0 ** -1000
+    A[1::3, :, 2::7] *= 2.0 ** -1060
+    B[::2, 3, :] *= 2.0 ** -1010
+    for alpha, beta in ((1.0, 0.0), (-0.75, 1.5)):
+        for i, (G, Am, Bm, C0) in enumerate(_run(h, s, A, B, C, m, n, k, alpha, beta)):
+            if i % 8 == 0 or i >= batch - 24:
+                ref = P.int8_emulated_gemm(Am, Bm, s, alpha, beta, C0)
+                assert np.array_equal(G.view(np.int64), ref.view(np.int64)), i
