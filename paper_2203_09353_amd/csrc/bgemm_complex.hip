@@ -18,9 +18,10 @@
 // one lane for the complex epilogue, and a lane group's sixteen rows are 256
 // contiguous bytes of a C column.
 //
-// Tile: 64 x 64 complex C per workgroup, four waves of 64 x 16, eight complex k
-// per step, a ring of three LDS stages filled by direct global-to-LDS loads
-// two steps ahead, three workgroups per CU.  What bounds it: the matrix cores
+// Tile: 64 x 64 complex C per workgroup (64 x 32 or 64 x 16 for fewer columns),
+// a wave per 16 columns, eight complex k per step, a ring of three LDS stages
+// filled by direct global-to-LDS loads two steps ahead, three workgroups per CU
+// (four or five of the narrow ones).  What bounds it: the matrix cores
 // (a 256 x 256 x 128 product moves 1.57 MB for 67 MFLOP).
 // Measured: 10,000 x Psi Psi^H of 256 x 128 12.8 -> 10.5 ms (52.5 -> 64 TFLOP/s),
 // 64 of 2048 x 1024 38.6 -> 32.2 ms (68 TFLOP/s), 3,000 x 200 x 90 x 300 conjugated
@@ -45,12 +46,9 @@ typedef const AS_GLOBAL double* gcptr;
 typedef AS_LDS d2* uptr;             // a 16-byte unit in LDS: one complex element
 typedef const AS_LDS d2* ucptr;
 
-constexpr int BM = 64, BN = 64, BK = 8, NS = 3, NT = 256, NW = NT / 64;
+constexpr int BM = 64, BK = 8, NS = 3;
 constexpr int WM = 64, WN = 16, FP = WM / 16, GQ = WN / 4;
-constexpr int PU = BM * BK / NT;          // units per thread, operand and step
-constexpr int DPT = 2 * PU;               // its direct loads per step
-constexpr int STAGE = (BM + BN) * BK;     // units
-static_assert(BM == WM && BN == NW * WN && BM == BN, "one wave per 16 columns");
+static_assert(BM == WM, "one wave per 16 columns");
 
 // s_waitcnt immediate: vector-memory count vm, LDS/scalar count lgkm, export
 // count unconstrained (gfx9 encoding)
@@ -85,17 +83,22 @@ struct Tile {
   }
 };
 
-// Three waves per SIMD (three workgroups per CU, as many as the LDS holds)
-// need at most 170 registers, which the compiler reaches without a spill (the
-// build checks: a spill would enter the counted waits).
-template <int TA, int TB>
-__global__ __launch_bounds__(NT, 3) void k_uniform_z(
+// Three waves per SIMD (three 64-wide workgroups per CU, as many as the LDS
+// holds) need at most 170 registers, two (the narrow tiles) 256, which the
+// compiler reaches without a spill (the build checks: a spill would enter the
+// counted waits).
+template <int TA, int TB, int BN>
+__global__ __launch_bounds__(BN * 4, BN == 64 ? 3 : 2) void k_uniform_z(
     int M, int N, int K, double ar, double ai, const double* const* __restrict__ Ap, int64_t lda,
     const double* const* __restrict__ Bp, int64_t ldb, double br, double bi,
     double* const* __restrict__ Cp, int64_t ldc, int tiles_m, int tiles_per_inst,
     int64_t total_tiles, int64_t per_xcd) {
   // the epilogue's complex products round as written (no fused multiply-add)
 #pragma clang fp contract(off)
+  constexpr int NT = BN * 4, NW = NT / 64;
+  constexpr int PA = BM * BK / NT, PB = BN * BK / NT;   // units per thread and step
+  constexpr int DPT = PA + PB;                          // its direct loads per step
+  constexpr int STAGE = (BM + BN) * BK;                 // units
   using TAt = Tile<BM, TA != 0>;
   using TBt = Tile<BN, TB == 0>;
   __shared__ __align__(16) double lds_raw[2 * NS * STAGE];
@@ -119,17 +122,17 @@ __global__ __launch_bounds__(NT, 3) void k_uniform_z(
   // column: in bounds, every wave issues the same number of direct loads (the
   // stage waits count them), and their products only reach C elements outside
   // C.
-  int64_t oa[PU], ob[PU];
-  int ka[PU], kb[PU];
+  int64_t oa[PA], ob[PB];
+  int ka[PA], kb[PB];
 #pragma unroll
-  for (int i = 0; i < PU; ++i) {
+  for (int i = 0; i < PA; ++i) {
     int mn;
     TAt::at((i * NW + wave) * 64 + lane, mn, ka[i]);
     const int64_t r = m0 + mn < M ? m0 + mn : m0;
     oa[i] = TA == 0 ? r + ka[i] * lda : ka[i] + r * lda;
   }
 #pragma unroll
-  for (int i = 0; i < PU; ++i) {
+  for (int i = 0; i < PB; ++i) {
     int mn;
     TBt::at((i * NW + wave) * 64 + lane, mn, kb[i]);
     const int64_t c = n0 + mn < N ? n0 + mn : n0;
@@ -147,13 +150,13 @@ __global__ __launch_bounds__(NT, 3) void k_uniform_z(
       // direct loads issued before it, whatever this wave's lanes hold.
       const int k0 = kt * BK;
 #pragma unroll
-      for (int i = 0; i < PU; ++i) {
+      for (int i = 0; i < PA; ++i) {
         const int over = k0 + ka[i] >= K ? k0 + ka[i] - (K - 1) : 0;
         const d2 x = *(const AS_GLOBAL d2u*)(A + 2 * (oa[i] + kt * sa - over * (TA == 0 ? lda : 1)));
         la[(i * NW + wave) * 64 + lane] = over ? d2{0.0, 0.0} : x;
       }
 #pragma unroll
-      for (int i = 0; i < PU; ++i) {
+      for (int i = 0; i < PB; ++i) {
         const int over = k0 + kb[i] >= K ? k0 + kb[i] - (K - 1) : 0;
         const d2 x = *(const AS_GLOBAL d2u*)(B + 2 * (ob[i] + kt * sb - over * (TB == 0 ? 1 : ldb)));
         lb[(i * NW + wave) * 64 + lane] = over ? d2{0.0, 0.0} : x;
@@ -161,11 +164,11 @@ __global__ __launch_bounds__(NT, 3) void k_uniform_z(
       __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
     } else {
 #pragma unroll
-      for (int i = 0; i < PU; ++i)
+      for (int i = 0; i < PA; ++i)
         __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)(A + 2 * (oa[i] + kt * sa)),
                                          (AS_LDS void*)(la + (i * NW + wave) * 64), 16, 0, 0);
 #pragma unroll
-      for (int i = 0; i < PU; ++i)
+      for (int i = 0; i < PB; ++i)
         __builtin_amdgcn_global_load_lds((const AS_GLOBAL void*)(B + 2 * (ob[i] + kt * sb)),
                                          (AS_LDS void*)(lb + (i * NW + wave) * 64), 16, 0, 0);
     }
@@ -255,27 +258,32 @@ __global__ __launch_bounds__(NT, 3) void k_uniform_z(
   // wn0 + 4 g + j of slab t, group g.
   const bool read_c = !(br == 0.0 && bi == 0.0);
   const int row0 = m0 + 4 * ((lane >> 2) & 3) + (lane >> 4);
+  // Every value of C is asked for before the first is used: 8,003 x 107 x 64 x 14
+  // with beta 1 took 567 us a column group at a time, 427 so.
+  d2 cv[GQ][FP];
+  if (read_c) {
 #pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    const int c = n0 + wn0 + 4 * g + lj;
-    d2 cv[FP];
-    if (read_c) {
+    for (int g = 0; g < GQ; ++g)
 #pragma unroll
-      for (int t = 0; t < FP; ++t)
+      for (int t = 0; t < FP; ++t) {
+        const int c = n0 + wn0 + 4 * g + lj;
         if (row0 + 16 * t < M && c < N)
-          cv[t] = *(const AS_GLOBAL d2u*)(C + 2 * (row0 + 16 * t + (int64_t)c * ldc));
-    }
+          cv[g][t] = *(const AS_GLOBAL d2u*)(C + 2 * (row0 + 16 * t + (int64_t)c * ldc));
+      }
+  }
+#pragma unroll
+  for (int g = 0; g < GQ; ++g)
 #pragma unroll
     for (int t = 0; t < FP; ++t) {
+      const int c = n0 + wn0 + 4 * g + lj;
       if (row0 + 16 * t >= M || c >= N) continue;
       d2 x{ar * cr[t][g] - ai * ci[t][g], ar * ci[t][g] + ai * cr[t][g]};
       if (read_c) {
-        x.x = x.x + (br * cv[t].x - bi * cv[t].y);
-        x.y = x.y + (br * cv[t].y + bi * cv[t].x);
+        x.x = x.x + (br * cv[g][t].x - bi * cv[g][t].y);
+        x.y = x.y + (br * cv[g][t].y + bi * cv[g][t].x);
       }
       *(AS_GLOBAL d2u*)(C + 2 * (row0 + 16 * t + (int64_t)c * ldc)) = x;
     }
-  }
 }
 
 // C <- beta C (complex), exactly zero when beta == 0 (C not read).
@@ -300,17 +308,30 @@ __global__ __launch_bounds__(256) void k_zscale(double br, double bi, double* co
   }
 }
 
-template <int TA, int TB>
-static hipError_t launch(const ZUniformArgs& a, hipStream_t s) {
+template <int TA, int TB, int BN>
+static hipError_t launch_tiles(const ZUniformArgs& a, hipStream_t s) {
   const int tiles_m = (a.m + BM - 1) / BM, tiles_n = (a.n + BN - 1) / BN;
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
   const int64_t total = tpi * a.batch;
   const int64_t per_xcd = (total + 7) / 8;
   if (tpi > INT32_MAX || per_xcd * 8 > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_uniform_z<TA, TB>), dim3((unsigned)(per_xcd * 8)), dim3(NT), 0, s, a.m, a.n,
-                     a.k, a.alpha[0], a.alpha[1], a.A, a.lda, a.B, a.ldb, a.beta[0], a.beta[1],
-                     a.C, a.ldc, tiles_m, (int)tpi, total, per_xcd);
+  hipLaunchKernelGGL((k_uniform_z<TA, TB, BN>), dim3((unsigned)(per_xcd * 8)), dim3(BN * 4), 0,
+                     s, a.m, a.n, a.k, a.alpha[0], a.alpha[1], a.A, a.lda, a.B, a.ldb, a.beta[0],
+                     a.beta[1], a.C, a.ldc, tiles_m, (int)tpi, total, per_xcd);
   return hipGetLastError();
+}
+
+// Tile width.  64 columns are the fastest where they are all C's (2,000 x 256^3:
+// 4.04 ms, 32 columns 4.39, 16 5.32), so 32 are taken where they leave a tenth
+// or more less padding: n = 24 (5,000 x 200 x 24 x 300) 2.01 -> 1.71 ms, n = 96
+// (5,000 x 200 x 96 x 100) 2.16 -> 1.89, n = 160 (2,000 x 256 x 160 x 200) 2.33 ->
+// 2.21.  16 only for n <= 16: 5,000 x 200 x 16 x 300 1.29 ms with 32, 1.20 with 16,
+// but n = 48 1.25 with 16 and 1.18 with 64.
+template <int TA, int TB>
+static hipError_t launch(const ZUniformArgs& a, hipStream_t s) {
+  if (a.n <= 16) return launch_tiles<TA, TB, 16>(a, s);
+  const int64_t w32 = ((int64_t)a.n + 31) / 32 * 32, w64 = ((int64_t)a.n + 63) / 64 * 64;
+  return 11 * w32 < 10 * w64 ? launch_tiles<TA, TB, 32>(a, s) : launch_tiles<TA, TB, 64>(a, s);
 }
 
 }  // namespace cplx

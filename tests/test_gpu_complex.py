@@ -91,6 +91,14 @@ def test_complex_tile_edges(h, m, n, k, ta, tb):
     run_case(h, ta, tb, m, n, k, 0.5j, 0.0, pads=(0, 1, 0), seed=4, c_nan=True)
 
 
+@pytest.mark.parametrize("n", [16, 18, 32, 33, 64, 96, 129, 160])
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "C"), ("C", "T"), ("T", "N")])
+def test_complex_tile_widths(h, n, ta, tb):
+    """Widths on both sides of each change of tile; exact on Gaussian integers."""
+    run_case(h, ta, tb, 65, n, 26, 2 - 1j, 1j, pads=(0, 2, 1), seed=6, integer=True)
+    run_case(h, ta, tb, 30, n, 8, 0.5j, 0.0, pads=(1, 0, 0), seed=7, c_nan=True)
+
+
 @pytest.mark.parametrize("ta,tb", list(itertools.product("NTC", "NTC")))
 def test_complex_gaussian_integers_exact(h, ta, tb):
     run_case(h, ta, tb, 70, 45, 100, 2 - 1j, 1 + 3j, integer=True, pads=(2, 1, 0), seed=3)
