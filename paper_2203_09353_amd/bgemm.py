@@ -124,6 +124,18 @@ def dgemm_vbatched_noalloc_raw(transa, transb, pm, pn, pk, alpha, pA, plda, pB, 
     return st, bad.value
 
 
+def _ld(x) -> int:
+    """Leading dimension of a stacked (batch, cols, ld) tensor or of the first
+    of a list.  The stack's own shape is read where it has instances: taking
+    x[0] makes a view (1.5 against 0.4 us), and three of them bounded small
+    calls (1,000 x 32^3: 10.6 us a call, 8.6 without)."""
+    if isinstance(x, torch.Tensor):
+        shape = x.shape
+        if len(shape) > 1 and shape[0]:
+            return shape[-1]
+    return x[0].shape[-1]
+
+
 def pointer_array(x) -> torch.Tensor:
     """Device int64 tensor of per-instance data pointers for a (batch, cols,
     ld) tensor or a list of tensors (kept alive by the caller)."""
@@ -205,8 +217,7 @@ class Handle:
                  ptrs=None):
         """Complex batch on stacked (batch, cols, ld) complex128 CUDA tensors
         (or lists of (cols, ld) tensors); ld in complex elements."""
-        a0, b0, c0 = A[0], B[0], C[0]
-        lda, ldb, ldc = a0.shape[-1], b0.shape[-1], c0.shape[-1]
+        lda, ldb, ldc = _ld(A), _ld(B), _ld(C)
         batch = C.shape[0] if isinstance(C, torch.Tensor) else len(C)
         if ptrs is None:
             ptrs = (pointer_array(A), pointer_array(B), pointer_array(C))
@@ -251,8 +262,7 @@ class Handle:
         tensors or lists of (cols, ld) tensors; the leading dimensions are read
         from the last axis.  ``ptrs`` may pass precomputed (pA, pB, pC)
         pointer tensors.  Returns the pointer tensors."""
-        a0, b0, c0 = A[0], B[0], C[0]
-        lda, ldb, ldc = a0.shape[-1], b0.shape[-1], c0.shape[-1]
+        lda, ldb, ldc = _ld(A), _ld(B), _ld(C)
         batch = C.shape[0] if isinstance(C, torch.Tensor) else len(C)
         if ptrs is None:
             ptrs = (pointer_array(A), pointer_array(B), pointer_array(C))
@@ -271,8 +281,7 @@ class Handle:
         mode = MODES.get(mode, mode) if isinstance(mode, str) else mode
         if isinstance(mode, str):
             raise ValueError("unknown mode " + mode)
-        a0, b0, c0 = A[0], B[0], C[0]
-        lda, ldb, ldc = a0.shape[-1], b0.shape[-1], c0.shape[-1]
+        lda, ldb, ldc = _ld(A), _ld(B), _ld(C)
         batch = C.shape[0] if isinstance(C, torch.Tensor) else len(C)
         if ptrs is None:
             ptrs = (pointer_array(A), pointer_array(B), pointer_array(C))
