@@ -521,7 +521,11 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
 // shape on 158 ragged sizes in 8..513; there the choice is within 0.7 % of the
 // best shape on average, and 1.43x the speed of three classes by max(m, n).  An
 // instance that is a single 64 x 64 tile and short in k is bound by memory and
-// prefers two half tiles in flight (200,000 x 64^3 4.45 against 4.37 ms).  A batch
+// prefers two half tiles in flight (200,000 x 64^3 4.45 against 4.37 ms).  At one
+// k-step C is most of the traffic, and tiles of 32 rows leave each column of a
+// taller C to several workgroups, 256 bytes apiece (5,540 x 400 x 112 x 8 774 us on
+// 32 x 64 and 696 on 64 x 64, 20,000 x 96 x 96 x 16 474 and, on 64 x 32, 434, but
+// 20,000 x 90 x 90 x 16 608 and 630).  A batch
 // that would not give every CU `need` tiles of a shape goes to a finer one: a
 // short batch is latency-bound, and more, shorter tiles finish sooner (1 x 512^3
 // 22.1 us on 64 x 64, 14.7 on 64 x 32 and 14.2 on 32 x 32 tiles; 7 x 512^3 37.5 / 38.2
@@ -552,6 +556,7 @@ TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int fo
     const double used = up(m, 32) * up(n, t.wn / 2);
     double cost = t.weight * k16 * (PADDED * area + (1 - PADDED) * used) + t.fixed * area;
     if (t.cls == TC_64 && tiles == 1.0 && k <= 128) cost *= 1.08;
+    if (t.cls == TC_32x64 && m > 32 && k <= 16) cost *= 1.12;
     if (least == 0.0 || cost < least) {
       least = cost;
       best = t.cls;
