@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "bgemm_internal.h"
+#include "bgemm_tiles.h"
 
 namespace bg {
 
@@ -103,45 +104,6 @@ constexpr int waitcnt_imm(int vm, int lgkm) {
 // read is served sixteen lanes at a time, eight from each of two lane groups);
 // with f = mn / 2 and rho, f trivial on Q, 40 % of the LDS's cycles were.
 // ---------------------------------------------------------------------------
-template <int BM_, int BN_, int WM_, int WN_>
-struct PCfg {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = 2, BK = 16;
-  static constexpr int WAVES_M = BM / WM, NW = WAVES_M * (BN / WN), NT = 64 * NW;
-  static constexpr int FP = WM / 16, GQ = WN / 4;    // slabs, column groups per wave
-  static constexpr int CA = BM * BK / 128, CB = BN * BK / 128;   // 1 KB chunks per stage
-  static constexpr int PA = (CA + NW - 1) / NW, PB = (CB + NW - 1) / NW;   // per wave
-  static constexpr int STAGE = (BM + BN) * BK / 2;   // units
-  static constexpr int LDS = NS * STAGE * 2;         // doubles
-  // workgroups that fit a CU's LDS, and the waves per SIMD they make
-  static constexpr int WGS = 163840 / (LDS * 8 + 64);
-  static constexpr int WAVES = WGS * NW / 4 > 8 ? 8 : (WGS * NW / 4 < 1 ? 1 : WGS * NW / 4);
-  static_assert(BM % WM == 0 && BN % WN == 0, "tile");
-  static_assert(WM == 32 || WM == 64, "one or two slab pairs");
-  static_assert(WN % 16 == 0, "a wave starts at a whole turn of the Q swizzle");
-};
-
-template <int EXT, int BK, bool KC, bool ROLE_P>
-struct PTile {
-  static_assert(BK == 16, "rows of eight units");
-  static constexpr int UR = KC ? BK / 2 : EXT / 2;   // units per row
-  __device__ __forceinline__ static int rho(int mn) {
-    return (mn & ~3) | ((mn & 1) << 1) | ((mn >> 1) & 1);
-  }
-  __device__ __forceinline__ static int f(int mn) {
-    return (ROLE_P ? (mn >> 2) & 7 : 0) ^ (2 * (mn & 1));
-  }
-  // first element of the unit at position p
-  __device__ __forceinline__ static void at(int p, int& mn, int& k) {
-    if (KC) {
-      mn = rho(p / UR);
-      k = 2 * ((p % UR) ^ f(mn));
-    } else {
-      k = p / UR;
-      mn = 2 * ((p % UR) ^ (ROLE_P ? 0 : 4 * ((k >> 1) & 1)));
-    }
-  }
-};
-
 typedef AS_LDS d2* uptr;
 typedef const AS_LDS d2* ucptr;
 
@@ -165,8 +127,7 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
   // persistent caller's tiles
   asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave % CF::WAVES_M) * CF::WM, wn0 = (wave / CF::WAVES_M) * CF::WN;
-  const int ls = lane >> 4, lr = lane & 15, lj = lane & 3;
+  const int wm0 = CF::wave_row(wave), wn0 = CF::wave_col(wave);
   const bool use_product = !(alpha == 0.0 || K == 0);
 
   double acc[FP][GQ];
@@ -187,6 +148,7 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
     // then serves them all.
     constexpr bool STEP_A = !AK && NW * 64 % At::UR == 0 && CF::CA % NW == 0;
     constexpr bool STEP_B = !BKC && NW * 64 % Bt::UR == 0 && CF::CB % NW == 0;
+    static_assert(!STEP_B || NW * 64 / Bt::UR % 4 == 0, "whole turns of the Q swizzle apart");
     constexpr int QA = STEP_A ? 1 : CF::PA, QB = STEP_B ? 1 : CF::PB;
     gcptr pa[QA], pb[QB];
 #pragma unroll
@@ -266,25 +228,12 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
     };
     issue(0, 0);
 
-    // Lane addresses of the fragment reads; everything else is a constant
-    // offset.  Half slice tp of a step holds k = 2 ls + 8 tp and the next, unit
-    // ls + 4 tp of a K-contiguous row.
-    int ap[AK ? 4 : 1], bp[BKC ? 1 : 2];
-    if constexpr (AK) {   // rows 2 lr + u of a slab pair
+    // lane addresses of the fragment reads; everything else is a constant offset
+    int ap[At::BASES], bp[Bt::BASES];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)   // v = 2 tp + u
-        ap[v] = (wm0 + At::rho(2 * lr + (v & 1))) * 8 +
-                ((ls + 4 * (v >> 1)) ^ At::f(2 * lr + (v & 1)));
-    } else {
-      ap[0] = 2 * ls * At::UR + wm0 / 2 + lr;
-    }
-    if constexpr (BKC) {  // row 4 g + lj
-      bp[0] = A_UNITS + (wn0 + Bt::rho(lj)) * 8 + (ls ^ Bt::f(lj));
-    } else {
+    for (int v = 0; v < At::BASES; ++v) ap[v] = At::p_base(wm0, lane, v);
 #pragma unroll
-      for (int v = 0; v < 2; ++v)   // v = column octet & 1
-        bp[v] = A_UNITS + 2 * ls * Bt::UR + wn0 / 2 + lj + 4 * ((ls & 1) ^ v);
-    }
+    for (int v = 0; v < Bt::BASES; ++v) bp[v] = A_UNITS + Bt::q_base(wn0, lane, v);
 
     // Step kt lives in stage kt mod 2.  Its loads were issued a step ago; the
     // wait and the barrier publish every wave's part, and only after it is the
@@ -314,13 +263,9 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
           for (int a = 0; a < NPA / 2; ++a)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              if constexpr (AK) {
-                const d2 x = stage[ap[AK ? 2 * tp + u : 0] + 32 * a * 8];
-                fp[2 * a + u][0] = x.x; fp[2 * a + u][1] = x.y;
-              } else {
-                const d2 x = stage[ap[0] + (8 * tp + u) * At::UR + 16 * a];
-                fp[2 * a][u] = x.x; fp[2 * a + 1][u] = x.y;
-              }
+              const d2 x = stage[ap[AK ? 2 * tp + u : 0] + At::p_offset(tp, u, a)];
+              if constexpr (AK) { fp[2 * a + u][0] = x.x; fp[2 * a + u][1] = x.y; }
+              else { fp[2 * a][u] = x.x; fp[2 * a + 1][u] = x.y; }
             }
           // Q groups two at a time: more live fragments would cost the
           // registers of a resident workgroup
@@ -329,13 +274,9 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
             double fq[2][2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              if constexpr (BKC) {
-                const d2 x = stage[bp[0] + 4 * (h + u) * 8 + 4 * tp];
-                fq[u][0] = x.x; fq[u][1] = x.y;
-              } else {
-                const d2 x = stage[bp[BKC ? 0 : (h / 2) & 1] + (8 * tp + u) * Bt::UR + 8 * (h / 4)];
-                fq[0][u] = x.x; fq[1][u] = x.y;
-              }
+              const d2 x = stage[bp[BKC ? 0 : (h / 2) & 1] + Bt::q_offset(tp, u, h)];
+              if constexpr (BKC) { fq[u][0] = x.x; fq[u][1] = x.y; }
+              else { fq[0][u] = x.x; fq[1][u] = x.y; }
             }
             if (tp == 1 && h == 0) refill();
 #pragma unroll
@@ -376,11 +317,9 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
   if (!use_product && beta == 1.0) return;
   int le;   // the lane again, not kept in a register through the k loop
   asm volatile("v_and_b32 %0, 63, %1" : "=v"(le) : "v"((int)threadIdx.x));
-  const int r0 = m0 + wm0 + 2 * (4 * ((le >> 2) & 3) + (le >> 4));
-  auto c_col = [&](int g) {
-    return n0 + wn0 + (BKC ? 4 * g + (le & 3) : 8 * (g / 2) + 2 * (le & 3) + (g & 1));
-  };
-  constexpr int GE = GQ > 8 ? 8 : GQ;
+  const int r0 = m0 + CF::lane_row(wm0, le);
+  auto c_col = [&](int g) { return n0 + CF::lane_col(BKC, wn0, le, g); };
+  constexpr int GE = CF::GE;
   auto combine = [&](int a, int g, d2 c) {
     // alpha acc is rounded, beta c fused: written out, since the compiler may
     // contract the plain sum either way and every class must round alike
@@ -422,7 +361,7 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
     else interior(std::false_type{});
     return;
   }
-  constexpr int GB = GQ > 4 ? 4 : GQ;   // edge tiles: bounds take registers too
+  constexpr int GB = CF::GB;   // edge tiles: bounds take registers too
 #pragma unroll
   for (int g0 = 0; g0 < GQ; g0 += GB) {
     d2 cv[FP / 2][GB];
@@ -453,16 +392,6 @@ __device__ __forceinline__ void pipe_tile(const double* A_, int64_t lda, const d
       }
   }
 }
-
-// Shapes: BM, BN, WM, WN.
-using P128 = PCfg<128, 128, 64, 64>;
-using P128x64 = PCfg<128, 64, 64, 32>;
-using P128x48 = PCfg<128, 48, 32, 48>;
-using P64 = PCfg<64, 64, 32, 32>;
-using P64x32 = PCfg<64, 32, 32, 16>;
-using P32x64 = PCfg<32, 64, 32, 16>;
-using P32 = PCfg<32, 32, 32, 16>;
-using P32x16 = PCfg<32, 16, 32, 16>;
 
 // ---------------------------------------------------------------------------
 // Uniform batch: one workgroup per (instance, C tile).  Workgroups are handed
