@@ -201,6 +201,17 @@ bg_status_t bg_set_uniform_class(bg_handle_t h, int cls) {
   return BG_STATUS_SUCCESS;
 }
 
+int bgi_pick_tile(int m, int n, int k, int batch, int num_cus) {
+  return bg::pick_uniform_class(m, n, k, batch, num_cus, -1);
+}
+
+bg_status_t bgi_force_tile(bg_handle_t h, int shape) {
+  if (!valid(h)) return BG_STATUS_INVALID_HANDLE;
+  if (shape < -1 || shape >= bg::TC_SHAPES) return BG_STATUS_INVALID_VALUE;
+  h->force_class = shape;
+  return BG_STATUS_SUCCESS;
+}
+
 int bg_check_batched_args(char transa, char transb, int m, int n, int k, const void* dA, int lda,
                           const void* dB, int ldb, const void* dC, int ldc, int batch) {
   const int ta = trans_code(transa), tb = trans_code(transb);

@@ -473,7 +473,7 @@ static const TileChoice kTiles[] = {
 constexpr double PADDED = 0.63;
 
 TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int force) {
-  if (force >= 0 && force < TC_COUNT) return (TileClass)force;
+  if (force >= 0 && force < TC_SHAPES) return (TileClass)force;
   auto up = [](int x, int to) { return (double)((x + to - 1) / to) * to; };
   const double k16 = up(k, 16);
   TileClass best = TC_128;   // the coarsest, should every grid be too large
