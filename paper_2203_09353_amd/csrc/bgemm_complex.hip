@@ -312,13 +312,13 @@ template <int TA, int TB, int BN>
 static hipError_t launch_tiles(const ZUniformArgs& a, hipStream_t s) {
   const int tiles_m = (a.m + BM - 1) / BM, tiles_n = (a.n + BN - 1) / BN;
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
-  const int64_t total = tpi * a.batch;
-  const int64_t per_xcd = (total + 7) / 8;
-  if (tpi > INT32_MAX || per_xcd * 8 > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_uniform_z<TA, TB, BN>), dim3((unsigned)(per_xcd * 8)), dim3(BN * 4), 0,
-                     s, a.m, a.n, a.k, a.alpha[0], a.alpha[1], a.A, a.lda, a.B, a.ldb, a.beta[0],
-                     a.beta[1], a.C, a.ldc, tiles_m, (int)tpi, total, per_xcd);
-  return hipGetLastError();
+  return launch_in_parts(tpi, a.batch, BN * 4, [&](int64_t b0, int64_t total, int64_t per_xcd,
+                                                   dim3 grid) {
+    hipLaunchKernelGGL((k_uniform_z<TA, TB, BN>), grid, dim3(BN * 4), 0, s, a.m, a.n, a.k,
+                       a.alpha[0], a.alpha[1], a.A + b0, a.lda, a.B + b0, a.ldb, a.beta[0],
+                       a.beta[1], a.C + b0, a.ldc, tiles_m, (int)tpi, total, per_xcd);
+    return hipGetLastError();
+  });
 }
 
 // Tile width.  64 columns are the fastest where they are all C's (2,000 x 256^3:

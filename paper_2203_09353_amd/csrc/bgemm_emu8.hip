@@ -468,8 +468,10 @@ static hipError_t launch(const UniformArgs& a, void* ws, size_t ws_bytes, hipStr
   const int tiles_m = (a.m + TM - 1) / TM, tiles_n = (a.n + BN - 1) / BN;
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
   const int nb = (a.m + 255) / 256 + (a.n + EXP_COLS - 1) / EXP_COLS;
-  // grid sizes stay within 32 bits
-  gmax = std::min<int64_t>(gmax, (int64_t)(INT32_MAX - 8) / std::max<int64_t>(tpi, nb));
+  // both launches of a group stay within the launch limit (the tile loop's grid
+  // does not grow with the group)
+  gmax = std::min<int64_t>(gmax, instances_per_launch(nb, 256));
+  gmax = std::min<int64_t>(gmax, S == 8 ? instances_per_launch(tpi, NT) : (INT32_MAX - 8) / tpi);
   if (gmax < 1) return hipErrorInvalidValue;
   for (int64_t b0 = 0; b0 < a.batch; b0 += gmax) {
     const int g = (int)std::min<int64_t>(gmax, a.batch - b0);

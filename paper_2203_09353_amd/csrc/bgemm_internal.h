@@ -34,6 +34,32 @@ TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int fo
 extern "C" int bgi_pick_tile(int m, int n, int k, int batch, int num_cus);
 extern "C" bg_status_t bgi_force_tile(bg_handle_t h, int shape);
 
+// Instances one launch may take at `blocks` workgroups of `threads` each (0: not
+// even one).  A launch counts its threads in 32 bits and drops the rest without
+// an error; workgroups are dealt to the XCDs in whole turns of eight.
+inline int64_t instances_per_launch(int64_t blocks, int threads) {
+  const int64_t most = (((int64_t)1 << 32) - 1) / threads / 8 * 8;
+  return most / blocks;
+}
+
+// Launches a uniform batch whose instances take `tiles` workgroups of `threads`
+// each, in as few parts as the launch limit allows: part(first instance, tiles of
+// the part, tiles per XCD, workgroups).  hipErrorInvalidValue for grids beyond
+// int32 over the whole batch.
+template <class Part>
+hipError_t launch_in_parts(int64_t tiles, int batch, int threads, Part part) {
+  if (tiles > INT32_MAX || (tiles * batch + 7) / 8 * 8 > INT32_MAX) return hipErrorInvalidValue;
+  const int64_t per = instances_per_launch(tiles, threads);
+  if (per < 1) return hipErrorInvalidValue;
+  for (int64_t first = 0; first < batch; first += per) {
+    const int64_t total = tiles * (batch - first < per ? batch - first : per);
+    const int64_t per_xcd = (total + 7) / 8;
+    const hipError_t e = part(first, total, per_xcd, dim3((unsigned)(per_xcd * 8)));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct UniformArgs {
   bool ta, tb;
   int m, n, k;

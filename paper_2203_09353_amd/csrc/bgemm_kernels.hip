@@ -422,15 +422,13 @@ static hipError_t launch_uniform_t(const UniformArgs& a, hipStream_t s) {
   const int tiles_m = (a.m + CF::BM - 1) / CF::BM;
   const int tiles_n = (a.n + CF::BN - 1) / CF::BN;
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
-  const int64_t total = tpi * a.batch;
-  if (tpi > INT32_MAX) return hipErrorInvalidValue;
-  const int64_t per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
-  const int64_t grid = per_xcd * NUM_XCD;
-  if (grid > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_uniform<CF, TA, TB>), dim3((unsigned)grid), dim3(CF::NT), 0, s, a.m, a.n,
-                     a.k, a.alpha, a.A, a.lda, a.B, a.ldb, a.beta, a.C, a.ldc, tiles_m, (int)tpi,
-                     total, per_xcd);
-  return hipGetLastError();
+  return launch_in_parts(tpi, a.batch, CF::NT, [&](int64_t b0, int64_t total, int64_t per_xcd,
+                                                   dim3 grid) {
+    hipLaunchKernelGGL((k_uniform<CF, TA, TB>), grid, dim3(CF::NT), 0, s, a.m, a.n, a.k, a.alpha,
+                       a.A + b0, a.lda, a.B + b0, a.ldb, a.beta, a.C + b0, a.ldc, tiles_m, (int)tpi,
+                       total, per_xcd);
+    return hipGetLastError();
+  });
 }
 
 template <class CF>

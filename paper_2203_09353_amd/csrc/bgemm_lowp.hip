@@ -287,13 +287,13 @@ template <int MODE, int S>
 static hipError_t launch(const UniformArgs& a, hipStream_t s) {
   const int tiles_m = (a.m + BM - 1) / BM, tiles_n = (a.n + BN - 1) / BN;
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
-  const int64_t total = tpi * a.batch;
-  const int64_t per_xcd = (total + 7) / 8;
-  if (tpi > INT32_MAX || per_xcd * 8 > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_lowp<MODE, S>), dim3((unsigned)(per_xcd * 8)), dim3(NT), 0, s, a.m, a.n, a.k,
-                     a.alpha, a.A, a.lda, a.B, a.ldb, a.beta, a.C, a.ldc, tiles_m, (int)tpi, total,
-                     per_xcd);
-  return hipGetLastError();
+  return launch_in_parts(tpi, a.batch, NT, [&](int64_t b0, int64_t total, int64_t per_xcd,
+                                               dim3 grid) {
+    hipLaunchKernelGGL((k_lowp<MODE, S>), grid, dim3(NT), 0, s, a.m, a.n, a.k, a.alpha, a.A + b0,
+                       a.lda, a.B + b0, a.ldb, a.beta, a.C + b0, a.ldc, tiles_m, (int)tpi, total,
+                       per_xcd);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace lowp
