@@ -201,8 +201,8 @@ bg_status_t bg_set_uniform_class(bg_handle_t h, int cls) {
   return BG_STATUS_SUCCESS;
 }
 
-int bgi_pick_tile(int m, int n, int k, int batch, int num_cus) {
-  return bg::pick_uniform_class(m, n, k, batch, num_cus, -1);
+int bgi_pick_tile(int nn, int m, int n, int k, int batch, int num_cus) {
+  return bg::pick_uniform_class(nn != 0, m, n, k, batch, num_cus, -1);
 }
 
 bg_status_t bgi_force_tile(bg_handle_t h, int shape) {
@@ -260,7 +260,8 @@ bg_status_t bg_dgemm_batched(bg_handle_t h, char transa, char transb, int m, int
     a.A = dA; a.lda = lda; a.B = dB; a.ldb = ldb; a.C = dC; a.ldc = ldc;
     a.batch = batch;
     a.num_cus = h->num_cus;
-    const bg::TileClass cls = bg::pick_uniform_class(m, n, k, batch, h->num_cus, h->force_class);
+    const bg::TileClass cls =
+        bg::pick_uniform_class(!a.ta && !a.tb, m, n, k, batch, h->num_cus, h->force_class);
     e = bg::launch_uniform(a, cls, h->stream);
     if (e == hipErrorInvalidValue) return BG_STATUS_NOT_SUPPORTED;
   }

@@ -24,14 +24,15 @@ enum TileClass : int {
   TC_SHAPES = 8
 };
 
-// Picks the tile class for a uniform batch of `batch` instances on a device
-// of `num_cus` compute units; `force` >= 0 overrides.
-TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int force);
+// Picks the tile class for a uniform batch of `batch` instances (`nn`: neither
+// operand transposed) on a device of `num_cus` compute units; `force` >= 0
+// overrides.
+TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cus, int force);
 
 // For tests and timing, exported beside the public interface: the shape that a
 // uniform batch takes by default, and a handle's override by any of the shapes
 // (-1 none; bg_set_uniform_class knows the first three).
-extern "C" int bgi_pick_tile(int m, int n, int k, int batch, int num_cus);
+extern "C" int bgi_pick_tile(int nn, int m, int n, int k, int batch, int num_cus);
 extern "C" bg_status_t bgi_force_tile(bg_handle_t h, int shape);
 
 // Instances one launch may take at `blocks` workgroups of `threads` each (0: not

@@ -440,19 +440,21 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
 }
 
 // Tile of a uniform batch: the one with the least estimated time.  Per C element
-// and k a tile takes `weight` (times of 400 x 512^3: 128 x 128 1,736 us, 128 x 64
-// 1,786, 64 x 64 1,873, 64 x 32 1,991, 32 x 64 1,994), and `fixed` k more for its
-// first loads and its C.  Of the area, what the matrix-core instructions of
-// edge waves skip counts by PADDED only (its loads and its slot remain).  The
-// fixed parts, PADDED and the weights of the last three fit the times of every
-// shape on 158 ragged sizes in 8..513; there the choice is within 0.7 % of the
-// best shape on average, and 1.43x the speed of three classes by max(m, n).  An
-// instance that is a single 64 x 64 tile and short in k is bound by memory and
-// prefers two half tiles in flight (200,000 x 64^3 4.45 against 4.37 ms).  At one
-// k-step C is most of the traffic, and tiles of 32 rows leave each column of a
-// taller C to several workgroups, 256 bytes apiece (5,540 x 400 x 112 x 8 774 us on
-// 32 x 64 and 696 on 64 x 64, 20,000 x 96 x 96 x 16 474 and, on 64 x 32, 434, but
-// 20,000 x 90 x 90 x 16 608 and 630).  A batch
+// and k a tile takes `weight`, and `fixed` k more for its first loads and its C.
+// Of the area, what the matrix-core instructions of edge waves skip counts by
+// PADDED only (its loads and its slot remain).  All of it is fitted to the times
+// of every shape on 725 sizes in 7..513, whole and ragged, every operand layout,
+// with and without C and padding: there the choice is 0.6 % from the best shape
+// on average.  Times in us of the shapes in the table's order, the choice first:
+//   20,000 x 256^3      11,990 | 11,990 12,140 13,700 12,660 13,490 13,490 14,710 17,020
+//   1,000 x 512^3        4,204 |  4,204  4,314  4,604  4,465  4,778  4,768  5,196  5,824
+//   60,000 x 128^3       5,821 |  5,805  5,821  6,676  6,016  6,445  6,485  7,050  8,274
+//   15,000 x 256 x 144 x 80  2,497 | 3,683 2,669 2,497 2,676 2,719 2,945 3,048 3,439
+//   60,000 x 128 x 48 x 64   1,927 | 3,188 2,172 1,927 2,082 2,018 2,095 2,157 2,244
+// A single 64 x 64 tile of at most two k-steps, neither operand transposed, is
+// bound by memory and prefers two half tiles in flight: 64 x 32 against 64 x 64 is
+// 2.6 % faster on 37 sizes of k <= 16 and 2.1 % on 29 of k <= 32, alike on 30 of k
+// <= 64; with a transposed operand it is 7 % slower on seven of k <= 32.  A batch
 // that would not give every CU `need` tiles of a shape goes to a finer one: a
 // short batch is latency-bound, and more, shorter tiles finish sooner (1 x 512^3
 // 22.1 us on 64 x 64, 14.7 on 64 x 32 and 14.2 on 32 x 32 tiles; 7 x 512^3 37.5 / 38.2
@@ -462,28 +464,30 @@ struct TileChoice {
   int bm, bn, wn;
   double weight, fixed, need;
 };
-static const TileChoice kTiles[] = {
-    {TC_128, 128, 128, 64, 1.00, 19, 2},   {TC_128x64, 128, 64, 32, 1.03, 5, 2},
-    {TC_128x48, 128, 48, 48, 1.057, 15, 2}, {TC_64, 64, 64, 32, 1.08, 4, 1},
-    {TC_64x32, 64, 32, 16, 1.147, 3.5, .5}, {TC_32x64, 32, 64, 16, 1.149, 3, .5},
-    {TC_32, 32, 32, 16, 1.163, 17, 0},      {TC_32x16, 32, 16, 16, 1.416, 21, 0},
+static constexpr TileChoice kTiles[] = {
+    {TC_128, 128, 128, 64, 1.000, 9.5, 2},   {TC_128x64, 128, 64, 32, 1.022, 4.5, 2},
+    {TC_128x48, 128, 48, 48, 1.083, 5.5, 2}, {TC_64, 64, 64, 32, 1.042, 4, 1},
+    {TC_64x32, 64, 32, 16, 1.137, 3, .5},    {TC_32x64, 32, 64, 16, 1.138, 4, .5},
+    {TC_32, 32, 32, 16, 1.334, 5, 0},        {TC_32x16, 32, 16, 16, 2.040, 7.5, 0},
 };
-constexpr double PADDED = 0.63;
+constexpr double PADDED = 0.66;
 
-TileClass pick_uniform_class(int m, int n, int k, int batch, int num_cus, int force) {
+TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cus, int force) {
   if (force >= 0 && force < TC_SHAPES) return (TileClass)force;
   auto up = [](int x, int to) { return (double)((x + to - 1) / to) * to; };
   const double k16 = up(k, 16);
+  const bool halves = nn && m > 32 && m <= 64 && n > 32 && n <= 64 && k <= 32;
   TileClass best = TC_128;   // the coarsest, should every grid be too large
   double least = 0.0;
+  // unrolled: the table's sizes are constants, and no division is left (0.2 us a call)
+#pragma unroll
   for (const TileChoice& t : kTiles) {
     const double area = up(m, t.bm) * up(n, t.bn);
-    const double tiles = area / (t.bm * t.bn);
+    const double tiles = area * (1.0 / (t.bm * t.bn));
     if (tiles * batch < t.need * num_cus || tiles * batch > INT32_MAX - 8) continue;
     const double used = up(m, 32) * up(n, t.wn / 2);
     double cost = t.weight * k16 * (PADDED * area + (1 - PADDED) * used) + t.fixed * area;
-    if (t.cls == TC_64 && tiles == 1.0 && k <= 128) cost *= 1.08;
-    if (t.cls == TC_32x64 && m > 32 && k <= 16) cost *= 1.12;
+    if (t.cls == TC_64x32 && halves) cost *= 0.92;
     if (least == 0.0 || cost < least) {
       least = cost;
       best = t.cls;
@@ -568,7 +572,7 @@ hipError_t launch_square_groups(const SquareGroup* groups, int count, int num_cu
     a.A = q.A; a.lda = q.n; a.B = q.B; a.ldb = q.n; a.C = q.C; a.ldc = q.n;
     a.batch = q.batch;
     const hipError_t e =
-        launch_uniform(a, pick_uniform_class(q.n, q.n, q.n, q.batch, num_cus, -1), s);
+        launch_uniform(a, pick_uniform_class(true, q.n, q.n, q.n, q.batch, num_cus, -1), s);
     if (e != hipSuccess) return e;
   }
   // the short ones, MAX_GROUPS to a launch; tile shapes as for one short batch

@@ -31,7 +31,7 @@ def test_every_shape_covers_its_tile_once(tmp_path):
 def test_a_batch_of_each_shape(shape, m, n, k, batch):
     """Sizes that take each tile shape by default on 256 compute units: a change
     of the rule that leaves a shape to no one shows here."""
-    assert bgemm.lib().bgi_pick_tile(m, n, k, batch, 256) == shape
+    assert bgemm.lib().bgi_pick_tile(1, m, n, k, batch, 256) == shape
 
 
 def test_override_refuses_unknown_shapes_and_handles():
