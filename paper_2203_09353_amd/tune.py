@@ -6,8 +6,10 @@ variable-size batch are the ``BG_CFGVB_*`` macros of
 ``csrc/bgemm_kernels.hip`` (BM, BN, WM, WN).
 The tuner compiles one library per candidate shape of a class, times each on
 that class's workload through the C ABI, and records the winner per
-(GPU architecture, class) in ``tune_cache.json``; ``build.py`` passes the
-cached shapes to hipcc.
+(GPU architecture, class) in ``tune_cache.json`` with every candidate's time;
+``build.py`` passes the cached shapes to hipcc.  A candidate is timed only if its
+results on that workload are those of the built library bit for bit (every shape
+sums in the same order).
 
     python -m paper_2203_09353_amd.tune build [--out DIR]     # CPU: compile candidates
     python -m paper_2203_09353_amd.tune run [--out DIR]       # GPU: time them, update the cache
@@ -101,13 +103,55 @@ def cmd_build(out: str):
             print(msg, flush=True)
 
 
-def _time_parts(lib_path, parts, reps=5):
+def _handle(lib_path):
+    from . import bgemm
+    bgemm._lib = None
+    bgemm.lib(lib_path)
+    return bgemm.Handle()
+
+
+def _c_of(part):
+    return part.C if hasattr(part, "C") else part.slabs[2]
+
+
+def _pass_results(lib_path, parts, start):
+    """Bits of C after one pass of the library over the parts, C as in `start`."""
     import torch
     from . import bgemm
     import bench  # the repository's benchmark driver (launch helpers)
+    h = _handle(lib_path)
+    out = []
+    for p, c0 in zip(parts, start):
+        _c_of(p).copy_(c0)
+        bench.part_launch(h, p)
+        torch.cuda.synchronize()
+        out.append(_c_of(p).view(torch.int64).clone())
+    h.close()
     bgemm._lib = None
-    bgemm.lib(lib_path)
-    h = bgemm.Handle()
+    return out
+
+
+def times_of_right(paths: dict, results, time) -> dict:
+    """{shape: time(path)} of the candidates `paths` ({shape: path}) that are built
+    and give the results of the built library (path None)."""
+    import torch
+    want = results(None)
+    out = {}
+    for shape, path in paths.items():
+        if not os.path.exists(path):   # not built (its kernels spill)
+            continue
+        if not all(torch.equal(a, b) for a, b in zip(results(path), want)):
+            print(json.dumps({"shape": shape, "left out": "results differ"}), flush=True)
+            continue
+        out[shape] = time(path)
+    return out
+
+
+def _time_parts(lib_path, parts, reps=5):
+    import torch
+    from . import bgemm
+    import bench
+    h = _handle(lib_path)
     total = 0.0
     for p in parts:
         for _ in range(2):
@@ -137,21 +181,20 @@ def cmd_run(out: str):
     for wl, macros in by_workload.items():
         parts = workloads.build(wl, "cuda")
         torch.cuda.synchronize()
+        start = [_c_of(p).clone() for p in parts]
         for macro in macros:
             cands = CANDIDATES[macro][1]
-            times = {}
-            for i, shape in enumerate(cands):
-                path = os.path.join(out, "libbgemm_%s.so" % _variant_name(macro, i))
-                if not os.path.exists(path):  # not built (its kernels spill)
-                    continue
-                ms = _time_parts(path, parts)
-                times[shape] = ms
+            paths = {shape: os.path.join(out, "libbgemm_%s.so" % _variant_name(macro, i))
+                     for i, shape in enumerate(cands)}
+            times = times_of_right(paths, lambda path: _pass_results(path, parts, start),
+                                   lambda path: _time_parts(path, parts))
+            for shape, ms in times.items():
                 print(json.dumps({"class": macro, "shape": shape, "workload": wl, "ms": round(ms, 4)}),
                       flush=True)
             best = pick(times, cands)
             entry[macro] = {"shape": best, "workload": wl, "ms": round(times[best], 4),
                             "candidates": {c: round(t, 4) for c, t in times.items()}}
-        del parts
+        del parts, start
         torch.cuda.empty_cache()
     with open(CACHE, "w") as f:
         json.dump(cache, f, indent=1, sort_keys=True)

@@ -36,3 +36,25 @@ def test_tuner_prefers_the_earlier_shape_on_a_tie():
     assert tune.pick({"a": 10.5, "b": 10.0, "c": 11.0}, order) == "b"      # a clearly slower
     assert tune.pick({"b": 10.0, "c": 9.0}, order) == "c"                  # a not built
     assert tune.pick({"c": 9.0}, order) == "c"
+
+
+def test_tuner_leaves_out_shapes_whose_results_differ(tmp_path):
+    """The fastest candidate is not timed, let alone recorded, if one value of its
+    results is off by a bit; one that is not built is passed over."""
+    import torch
+    from paper_2203_09353_amd import tune
+    right = torch.arange(6, dtype=torch.float64).view(torch.int64)
+    wrong = right.clone()
+    wrong[4] += 1
+    paths = {s: str(tmp_path / s) for s in ("a", "b", "c")}
+    for s in ("a", "b"):
+        (tmp_path / s).write_text("")
+    bits = {None: right, paths["a"]: wrong, paths["b"]: right.clone()}
+    asked = []
+
+    def time(path):
+        asked.append(path)
+        return {paths["a"]: 1.0, paths["b"]: 2.0}[path]
+
+    assert tune.times_of_right(paths, lambda p: [bits[p]], time) == {"b": 2.0}
+    assert asked == [paths["b"]]
