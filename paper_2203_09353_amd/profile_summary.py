@@ -25,7 +25,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 def kernel_source_hash() -> str:
     """sha256 over the kernel source and the tuned tile shapes."""
     h = hashlib.sha256()
-    for name in ("csrc/bgemm_kernels.hip", "tune_cache.json"):
+    for name in ("csrc/bgemm_kernels.hip", "csrc/bgemm_tiles.h", "tune_cache.json"):
         p = os.path.join(HERE, name)
         if os.path.exists(p):
             with open(p, "rb") as f:
@@ -52,7 +52,18 @@ def part_of(kernel_name: str, order: int) -> str:
     return "other"
 
 
-def durations_by_part(path: str) -> dict:
+def check_parts(dispatches: dict, workload: str):
+    """Raises unless every part of the workload has as many dispatches as every
+    other: parts are told apart by tile shape, and a change of the tile rule can
+    move one to another's shape."""
+    from . import workloads
+    want = workloads.ALIASES.get(workload, workload).split("+")
+    if sorted(dispatches) != sorted(want) or len(set(dispatches.values())) > 1:
+        raise ValueError("dispatches %s for the parts %s: tile shapes no longer tell the parts "
+                         "apart" % (dispatches, want))
+
+
+def durations_by_part(path: str, workload: str) -> dict:
     """Average device time per launch of each part from a --kernel-trace CSV:
     dispatches in start order; the 128-tile uniform launches alternate u256,
     s512 (the benchmark's part order); a variable-size launch is its planning
@@ -76,11 +87,12 @@ def durations_by_part(path: str) -> dict:
             p = part_of(name, order)
             launches[p] = launches.get(p, 0) + 1
         tot[p] = tot.get(p, 0.0) + ms
+    check_parts(launches, workload)
     return {p: (launches.get(p, 0), tot[p] / max(1, launches.get(p, 0))) for p in tot}
 
 
-def counter_by_part(path: str, counter: str) -> dict:
-    out = {}
+def counter_by_part(path: str, counter: str, workload: str) -> dict:
+    out, launches = {}, {}
     rows = [r for r in _rows(path) if r["Counter_Name"] == counter]
     rows.sort(key=lambda r: int(r["Dispatch_Id"]))
     big_seen = 0
@@ -92,6 +104,9 @@ def counter_by_part(path: str, counter: str) -> dict:
             big_seen += 1
         p = part_of(name, order)
         out[p] = out.get(p, 0.0) + float(r["Counter_Value"])
+        # of one step: the variable-size call is a dispatch per class
+        launches[p] = 1 if p == "vb" else launches.get(p, 0) + 1
+    check_parts(launches, workload)
     return out
 
 
@@ -114,8 +129,8 @@ def main():
     cw = [float(r["Counter_Value"]) for r in _rows(a.copy_write) if r["Counter_Name"] == "WRITE_SIZE"]
     fetch_factor = a.copy_bytes / (cf[-1] * 1024.0)
     write_factor = a.copy_bytes / (cw[-1] * 1024.0)
-    fetch = {k: v * 1024.0 * fetch_factor for k, v in counter_by_part(a.fetch, "FETCH_SIZE").items()}
-    write = {k: v * 1024.0 * write_factor for k, v in counter_by_part(a.write, "WRITE_SIZE").items()}
+    fetch = {k: v * 1024.0 * fetch_factor for k, v in counter_by_part(a.fetch, "FETCH_SIZE", a.workload).items()}
+    write = {k: v * 1024.0 * write_factor for k, v in counter_by_part(a.write, "WRITE_SIZE", a.workload).items()}
 
     stats = [r for r in _rows(a.stats) if "bg::" in r["Name"]]
     lines = ["# rocprofv3 summary: batched FP64 GEMM kernels, workload %s" % a.workload, "",
@@ -128,7 +143,7 @@ def main():
         lines.append("| `%s` | %s | %.3f | %.3f |" % (name, r["Calls"], float(r["AverageNs"]) / 1e6,
                                                      float(r["TotalDurationNs"]) / 1e6))
     if a.trace:
-        per = durations_by_part(a.trace)
+        per = durations_by_part(a.trace, a.workload)
         lines += ["", "Per part (device time of its kernels per launch; the two 128-tile uniform "
                   "launches of a step are u256 then s512):", "",
                   "| part | launches | average ms per launch |", "|---|---:|---:|"]

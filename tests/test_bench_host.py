@@ -5,6 +5,7 @@ import subprocess
 import sys
 
 import numpy as np
+import pytest
 
 import bench
 from paper_2203_09353_amd import profile_summary
@@ -46,6 +47,45 @@ def test_part_attribution_of_dispatches():
     assert profile_summary.part_of("void bg::k_uniform<bg::Cfg<64, 64, 16>>", 0) == "u64"
     assert profile_summary.part_of("void bg::k_uniform<bg::Cfg<128, 64, 16>>", 0) == "u256"
     assert profile_summary.part_of("void bg::k_uniform<bg::Cfg<128, 64, 16>>", 1) == "s512"
+
+
+def _counter_csv(path, kernels):
+    path.write_text("Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value\n" + "".join(
+        '%d,"void bg::%s(int)",FETCH_SIZE,%d\n' % (i, k, i + 1) for i, k in enumerate(kernels)))
+    return str(path)
+
+
+def test_parts_that_share_a_shape_are_refused(tmp_path):
+    """A step's dispatches by part, and an error instead of another part's bytes
+    once the tile rule gives two parts the same shape (or one an unknown one)."""
+    vb = ["k_vb_exec<bg::PCfg<%s>, false>" % x for x in ("128, 64", "64, 64", "32, 32")]
+    step = ["k_uniform<bg::PCfg<64, 64, 32, 32>>", "k_uniform<bg::PCfg<128, 128, 64, 64>>",
+            "k_uniform<bg::PCfg<128, 128, 64, 64>>"]
+    f = _counter_csv(tmp_path / "a.csv", step + vb)
+    assert profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb") == {
+        "u64": 1.0, "u256": 2.0, "s512": 3.0, "vb": 4.0 + 5.0 + 6.0}
+    for first in ("k_uniform<bg::PCfg<32, 64, 32, 16>>", "k_uniform<bg::PCfg<128, 64, 64, 32>>"):
+        f = _counter_csv(tmp_path / "b.csv", [first] + step[1:] + vb)
+        with pytest.raises(ValueError):
+            profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb")
+    f = _counter_csv(tmp_path / "c.csv", (step + vb) * 2)      # not one step
+    with pytest.raises(ValueError):
+        profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb")
+
+
+def test_summary_is_void_after_a_change_of_the_shapes(tmp_path, monkeypatch):
+    """The hash that ties a traffic summary to the kernels covers the file of
+    the tile shapes as well as the kernels and the tuned shapes."""
+    names = ("csrc/bgemm_kernels.hip", "csrc/bgemm_tiles.h", "tune_cache.json")
+    (tmp_path / "csrc").mkdir()
+    for n in names:
+        (tmp_path / n).write_text(n)
+    monkeypatch.setattr(profile_summary, "HERE", str(tmp_path))
+    seen = {profile_summary.kernel_source_hash()}
+    for n in names:
+        (tmp_path / n).write_text("changed")
+        seen.add(profile_summary.kernel_source_hash())
+    assert len(seen) == 4
 
 
 def test_padded_variable_size_workload_across_fill_groups():
