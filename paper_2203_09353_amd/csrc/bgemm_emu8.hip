@@ -452,8 +452,9 @@ static hipError_t launch_group(const UniformArgs& a, int64_t b0, int g, int* ea,
   const int64_t tpi = (int64_t)tiles_m * tiles_n;
   const int64_t total = tpi * g;
   const int64_t per_xcd = (total + 7) / 8;
-  // Two workgroups per CU take all tiles between them, each XCD's its contiguous
-  // share; with eight digits one workgroup takes one tile.
+  // A grid of two workgroups per CU takes all tiles between them, each XCD's its
+  // contiguous share (from two digits on registers hold one of the two at a time,
+  // 137 to 256 a lane); with eight digits one workgroup takes one tile.
   const int64_t per = S == 8 ? per_xcd : std::min<int64_t>(per_xcd, std::max(1, a.num_cus / 4));
   hipLaunchKernelGGL((k_emu8<S>), dim3((unsigned)(per * 8)), dim3(NT), 0, s, a.m, a.n, a.k,
                      a.alpha, a.A + b0, a.lda, a.B + b0, a.ldb, a.beta, a.C + b0, a.ldc, ea, fb,

@@ -91,7 +91,7 @@ constexpr int waitcnt_imm(int vm, int lgkm) {
 // 12.0 ms, against eight waves of 16 x 64 on a 128 x 64 tile with three stages;
 // 3,000 x 129 x 513 x 257 transposed 3.95 -> 2.91 ms with the finer tiles, 100,000 x
 // 16^3 0.54 -> 0.23 against staging through registers.
-// 128 x 64 tiles of four 64 x 32 waves: 21.6 / 12.35 ms; 64 x 128: as 128 x 64;
+// 128 x 64 tiles of four 64 x 32 waves: 21.6 / 12.1 ms; 64 x 128: as 128 x 64;
 // 64 x 64 of 64 x 16 waves: 23.8 / 13.3 (with a slower clock, the others 23.0 /
 // 13.0); three stages of it 24.1 / 13.6; the refill right after the barrier
 // +1.5 %; Q groups eight, four or two at a time within 1 %, two need the fewest
@@ -443,9 +443,12 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
 // and k a tile takes `weight`, and `fixed` k more for its first loads and its C.
 // Of the area, what the matrix-core instructions of edge waves skip counts by
 // PADDED only (its loads and its slot remain).  All of it is fitted to the times
-// of every shape on 725 sizes in 7..513, whole and ragged, every operand layout,
-// with and without C and padding: there the choice is 0.6 % from the best shape
-// on average.  Times in us of the shapes in the table's order, the choice first:
+// of every shape on 1,285 batches, m, n, k in 7..513, whole and ragged, every
+// operand layout, with and without C and padding, two thirds of them streaming
+// from HBM and the others down to a few hundred instances (which stay in the
+// caches, so that padding costs more): the choice is 1.0 % from the best shape on
+// average there, 1.9 % on 200 batches that were not fitted.  Times in us of the
+// shapes in the table's order, the choice first:
 //   20,000 x 256^3      11,990 | 11,990 12,140 13,700 12,660 13,490 13,490 14,710 17,020
 //   1,000 x 512^3        4,204 |  4,204  4,314  4,604  4,465  4,778  4,768  5,196  5,824
 //   60,000 x 128^3       5,821 |  5,805  5,821  6,676  6,016  6,445  6,485  7,050  8,274
@@ -465,12 +468,12 @@ struct TileChoice {
   double weight, fixed, need;
 };
 static constexpr TileChoice kTiles[] = {
-    {TC_128, 128, 128, 64, 1.000, 9.5, 2},   {TC_128x64, 128, 64, 32, 1.022, 4.5, 2},
-    {TC_128x48, 128, 48, 48, 1.083, 5.5, 2}, {TC_64, 64, 64, 32, 1.042, 4, 1},
-    {TC_64x32, 64, 32, 16, 1.137, 3, .5},    {TC_32x64, 32, 64, 16, 1.138, 4, .5},
-    {TC_32, 32, 32, 16, 1.334, 5, 0},        {TC_32x16, 32, 16, 16, 2.040, 7.5, 0},
+    {TC_128, 128, 128, 64, 1.000, 14, 2},    {TC_128x64, 128, 64, 32, 1.026, 7.5, 2},
+    {TC_128x48, 128, 48, 48, 1.137, 8, 2},   {TC_64, 64, 64, 32, 1.138, 4, 1},
+    {TC_64x32, 64, 32, 16, 1.239, 3, .5},    {TC_32x64, 32, 64, 16, 1.178, 6, .5},
+    {TC_32, 32, 32, 16, 1.459, 5.5, 0},      {TC_32x16, 32, 16, 16, 1.729, 14.5, 0},
 };
-constexpr double PADDED = 0.66;
+constexpr double PADDED = 0.75;
 
 TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cus, int force) {
   if (force >= 0 && force < TC_SHAPES) return (TileClass)force;
@@ -479,7 +482,7 @@ TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cu
   const bool halves = nn && m > 32 && m <= 64 && n > 32 && n <= 64 && k <= 32;
   TileClass best = TC_128;   // the coarsest, should every grid be too large
   double least = 0.0;
-  // unrolled: the table's sizes are constants, and no division is left (0.2 us a call)
+  // unrolled: the sizes are constants, so no division is left (49 ns a call)
 #pragma unroll
   for (const TileChoice& t : kTiles) {
     const double area = up(m, t.bm) * up(n, t.bn);
@@ -487,7 +490,7 @@ TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cu
     if (tiles * batch < t.need * num_cus || tiles * batch > INT32_MAX - 8) continue;
     const double used = up(m, 32) * up(n, t.wn / 2);
     double cost = t.weight * k16 * (PADDED * area + (1 - PADDED) * used) + t.fixed * area;
-    if (t.cls == TC_64x32 && halves) cost *= 0.92;
+    if (t.cls == TC_64x32 && halves) cost *= 0.85;
     if (least == 0.0 || cost < least) {
       least = cost;
       best = t.cls;
