@@ -454,10 +454,11 @@ static hipError_t launch_uniform_c(const UniformArgs& a, hipStream_t s) {
 //   60,000 x 128^3       5,821 |  5,805  5,821  6,676  6,016  6,445  6,485  7,050  8,274
 //   15,000 x 256 x 144 x 80  2,497 | 3,683 2,669 2,497 2,676 2,719 2,945 3,048 3,439
 //   60,000 x 128 x 48 x 64   1,927 | 3,188 2,172 1,927 2,082 2,018 2,095 2,157 2,244
-// A single 64 x 64 tile of at most two k-steps, neither operand transposed, is
-// bound by memory and prefers two half tiles in flight: 64 x 32 against 64 x 64 is
-// 2.6 % faster on 37 sizes of k <= 16 and 2.1 % on 29 of k <= 32, alike on 30 of k
-// <= 64; with a transposed operand it is 7 % slower on seven of k <= 32.  A batch
+// A single 64 x 64 tile with neither operand transposed is bound by memory at
+// short k and prefers two half tiles in flight: 64 x 32 against 64 x 64 is 2.5 %
+// faster on 68 sizes of k <= 32, at k of 33 to 64 1.2 % faster on 16 with both
+// extents above 48 (200,000 x 64^3 4.40 against 4.44 ms) and 2.4 % slower on 16
+// others; with a transposed operand it is 4.6 % slower on 26 of k <= 32.  A batch
 // that would not give every CU `need` tiles of a shape goes to a finer one: a
 // short batch is latency-bound, and more, shorter tiles finish sooner (1 x 512^3
 // 22.1 us on 64 x 64, 14.7 on 64 x 32 and 14.2 on 32 x 32 tiles; 7 x 512^3 37.5 / 38.2
@@ -479,7 +480,8 @@ TileClass pick_uniform_class(bool nn, int m, int n, int k, int batch, int num_cu
   if (force >= 0 && force < TC_SHAPES) return (TileClass)force;
   auto up = [](int x, int to) { return (double)((x + to - 1) / to) * to; };
   const double k16 = up(k, 16);
-  const bool halves = nn && m > 32 && m <= 64 && n > 32 && n <= 64 && k <= 32;
+  const bool halves = nn && m > 32 && m <= 64 && n > 32 && n <= 64 &&
+                      k <= (m > 48 && n > 48 ? 64 : 32);
   TileClass best = TC_128;   // the coarsest, should every grid be too large
   double least = 0.0;
   // unrolled: the sizes are constants, so no division is left (49 ns a call)
