@@ -39,8 +39,9 @@ def _rows(path):
 
 
 def part_of(kernel_name: str, order: int) -> str:
-    """Part of the config2+vb step that a GEMM dispatch belongs to; the two
-    128-tile uniform launches come in the order u256, s512."""
+    """Part of the config2+vb step that a GEMM dispatch belongs to, by its kernel
+    alone (the uniform parts as the 64 x 64 and 128-row tiles run them, `order`
+    telling the two of the latter apart)."""
     if "k_vb_exec" in kernel_name:
         return "vb"
     if "k_uniform" in kernel_name:
@@ -52,26 +53,26 @@ def part_of(kernel_name: str, order: int) -> str:
     return "other"
 
 
-def check_parts(dispatches: dict, workload: str):
-    """Raises unless every part of the workload has as many dispatches as every
-    other: parts are told apart by tile shape, and a change of the tile rule can
-    move one to another's shape."""
+def uniform_parts(workload: str, dispatches: int) -> list:
+    """Part of each of a run's uniform dispatches, which come step after step in
+    the workload's order (two parts may run on one tile shape).  Raises unless
+    they are whole steps."""
     from . import workloads
-    want = workloads.ALIASES.get(workload, workload).split("+")
-    if sorted(dispatches) != sorted(want) or len(set(dispatches.values())) > 1:
-        raise ValueError("dispatches %s for the parts %s: tile shapes no longer tell the parts "
-                         "apart" % (dispatches, want))
+    parts = [p for p in workloads.ALIASES.get(workload, workload).split("+")
+             if not p.startswith("vb")]
+    if dispatches == 0 or dispatches % len(parts):
+        raise ValueError("%d uniform dispatches are not whole steps of %s" % (dispatches, parts))
+    return parts * (dispatches // len(parts))
 
 
 def durations_by_part(path: str, workload: str) -> dict:
     """Average device time per launch of each part from a --kernel-trace CSV:
-    dispatches in start order; the 128-tile uniform launches alternate u256,
-    s512 (the benchmark's part order); a variable-size launch is its planning
-    kernels plus one persistent kernel per class."""
+    dispatches in start order; a variable-size launch is its planning kernels
+    plus one persistent kernel per class."""
     rows = [r for r in _rows(path) if "bg::" in r["Kernel_Name"]]
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
+    uniform = iter(uniform_parts(workload, sum("k_uniform" in r["Kernel_Name"] for r in rows)))
     tot, launches = {}, {}
-    big = 0
     for r in rows:
         name = r["Kernel_Name"]
         ms = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e6
@@ -80,33 +81,26 @@ def durations_by_part(path: str, workload: str) -> dict:
             if "k_vb_count" in name:
                 launches["vb"] = launches.get("vb", 0) + 1
         else:
-            order = 0
-            if "k_uniform" in name and "Cfg<64, 64" not in name and "Cfg<32, 32" not in name:
-                order = big % 2
-                big += 1
-            p = part_of(name, order)
+            p = next(uniform) if "k_uniform" in name else part_of(name, 0)
             launches[p] = launches.get(p, 0) + 1
         tot[p] = tot.get(p, 0.0) + ms
-    check_parts(launches, workload)
     return {p: (launches.get(p, 0), tot[p] / max(1, launches.get(p, 0))) for p in tot}
 
 
 def counter_by_part(path: str, counter: str, workload: str) -> dict:
-    out, launches = {}, {}
+    """Counter totals of one step by part.  Raises if the file holds another
+    number of steps."""
     rows = [r for r in _rows(path) if r["Counter_Name"] == counter]
     rows.sort(key=lambda r: int(r["Dispatch_Id"]))
-    big_seen = 0
+    parts = uniform_parts(workload, sum("k_uniform" in r["Kernel_Name"] for r in rows))
+    if len(set(parts)) != len(parts):
+        raise ValueError("%d uniform dispatches are more than one step" % len(parts))
+    uniform = iter(parts)
+    out = {}
     for r in rows:
         name = r["Kernel_Name"]
-        order = 0
-        if "k_uniform" in name and "Cfg<64, 64" not in name and "Cfg<32, 32" not in name:
-            order = big_seen
-            big_seen += 1
-        p = part_of(name, order)
+        p = next(uniform) if "k_uniform" in name else part_of(name, 0)
         out[p] = out.get(p, 0.0) + float(r["Counter_Value"])
-        # of one step: the variable-size call is a dispatch per class
-        launches[p] = 1 if p == "vb" else launches.get(p, 0) + 1
-    check_parts(launches, workload)
     return out
 
 
@@ -144,8 +138,8 @@ def main():
                                                      float(r["TotalDurationNs"]) / 1e6))
     if a.trace:
         per = durations_by_part(a.trace, a.workload)
-        lines += ["", "Per part (device time of its kernels per launch; the two 128-tile uniform "
-                  "launches of a step are u256 then s512):", "",
+        lines += ["", "Per part (device time of its kernels per launch; a step's uniform launches "
+                  "come in the parts' order):", "",
                   "| part | launches | average ms per launch |", "|---|---:|---:|"]
         for p in ("u32", "u64", "u256", "s512", "vb"):
             if p in per:

@@ -55,22 +55,21 @@ def _counter_csv(path, kernels):
     return str(path)
 
 
-def test_parts_that_share_a_shape_are_refused(tmp_path):
-    """A step's dispatches by part, and an error instead of another part's bytes
-    once the tile rule gives two parts the same shape (or one an unknown one)."""
+def test_parts_are_told_apart_whatever_their_shapes(tmp_path):
+    """A step's dispatches by part, also where the tile rule gives two parts one
+    shape or a part a new one; a file that is not one whole step is refused."""
     vb = ["k_vb_exec<bg::PCfg<%s>, false>" % x for x in ("128, 64", "64, 64", "32, 32")]
-    step = ["k_uniform<bg::PCfg<64, 64, 32, 32>>", "k_uniform<bg::PCfg<128, 128, 64, 64>>",
-            "k_uniform<bg::PCfg<128, 128, 64, 64>>"]
-    f = _counter_csv(tmp_path / "a.csv", step + vb)
-    assert profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb") == {
-        "u64": 1.0, "u256": 2.0, "s512": 3.0, "vb": 4.0 + 5.0 + 6.0}
-    for first in ("k_uniform<bg::PCfg<32, 64, 32, 16>>", "k_uniform<bg::PCfg<128, 64, 64, 32>>"):
-        f = _counter_csv(tmp_path / "b.csv", [first] + step[1:] + vb)
-        with pytest.raises(ValueError):
-            profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb")
-    f = _counter_csv(tmp_path / "c.csv", (step + vb) * 2)      # not one step
-    with pytest.raises(ValueError):
-        profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb")
+    for shapes in (("64, 64, 32, 32", "128, 64, 64, 32", "128, 128, 64, 64"),
+                   ("64, 32, 32, 16", "128, 128, 64, 64", "128, 128, 64, 64"),
+                   ("32, 32, 32, 16",) * 3):
+        step = ["k_uniform<bg::PCfg<%s>>" % x for x in shapes]
+        f = _counter_csv(tmp_path / "a.csv", step + vb)
+        assert profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb") == {
+            "u64": 1.0, "u256": 2.0, "s512": 3.0, "vb": 4.0 + 5.0 + 6.0}
+        for other in ((step + vb) * 2, step[1:] + vb, vb):
+            f = _counter_csv(tmp_path / "b.csv", other)
+            with pytest.raises(ValueError):
+                profile_summary.counter_by_part(f, "FETCH_SIZE", "config2+vb")
 
 
 def test_summary_is_void_after_a_change_of_the_shapes(tmp_path, monkeypatch):
